@@ -285,8 +285,9 @@ int aqlm_backward(const void* codes, const uint16_t* codebooks, const uint16_t* 
  * least loss (ties: earlier beam entry, then smaller code); `sweeps` passes
  * over all positions; the best configuration is written back to `codes`
  * (in place).  Candidate losses are the entry's loss plus a change computed
- * incrementally in fp32 from H r and the H_jj block, as the paper describes
- * (fp32 and exact arithmetic can break near-ties differently).  `loss_out`
+ * incrementally from H r (kept in fp32) and the H_jj block, as the paper
+ * describes, in fp64 (H r's rounding can still break near-ties differently
+ * from exact arithmetic).  `loss_out`
  * (fp32 [d_out], may be NULL) receives each row's final loss, recomputed
  * exactly (fp64) from the returned codes.  Rows are searched in parallel (one
  * workgroup per row, the beam state in on-chip memory).

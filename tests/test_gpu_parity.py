@@ -814,6 +814,43 @@ def test_beam_search_matches_oracle(d_out, d_in, M, beam, sweeps):
     assert np.all(exact <= start * (1 + 1e-6))
 
 
+@pytest.mark.parametrize("d_out,d_in,M,beam,sweeps", [
+    (300, 24, 1, 3, 2),      # two rows per workgroup, a half tile of inputs, three of four entry slots
+    (600, 264, 2, 5, 1),     # three rows, five of eight slots
+    (2050, 64, 1, 2, 1),     # five rows per workgroup, the last workgroup with fewer
+    (9, 1160, 1, 2, 2),      # inputs beyond the tiles loaded before the steps
+    (270, 8, 4, 1, 3),       # one group
+    (5, 16, 8, 8, 0),        # no sweep: the exact loss of the given codes
+])
+def test_beam_search_shared_workgroups(d_out, d_in, M, beam, sweeps):
+    """Rows that share a workgroup, partly filled tiles and entry slots; every
+    third row has scale zero (all candidates tie: smallest codes win, exactly)
+    and the second half of each codebook repeats the first."""
+    print(f"[beam] d_out={d_out} d_in={d_in} M={M} beam={beam} sweeps={sweeps}", flush=True)
+    lay, w, h = _beam_inputs(31000 + d_in + M + beam, d_out, d_in, M)
+    lay.scales[::3] = 0
+    lay.codebooks[:, 128:] = lay.codebooks[:, :128]
+    w[1] = np.nan                                  # no finite score: the row keeps its codes
+    ok = np.arange(d_out) != 1
+    ref_codes, ref_loss = oracle.beam_search(w[ok], h, lay.codes[ok], lay.codebooks, lay.scales[ok], beam=beam,
+                                             sweeps=sweeps)
+    codes, cb, sc, _ = to_device(lay)
+    loss = aq().beam_search(torch.from_numpy(w).cuda(), torch.from_numpy(h).cuda(), codes, cb, sc, beam=beam,
+                            sweeps=sweeps)
+    torch.cuda.synchronize()
+    got = codes.cpu().numpy()
+    got_loss = loss.double().cpu().numpy()
+    assert np.array_equal(got[1], lay.codes[1]) and np.isnan(got_loss[1])
+    got, got_loss = got[ok], got_loss[ok]
+    exact = oracle.aq_loss(w[ok], h, got, lay.codebooks, lay.scales[ok])
+    np.testing.assert_allclose(got_loss, exact, rtol=1e-6)
+    np.testing.assert_allclose(exact, ref_loss, rtol=2e-3)
+    zero = np.asarray(lay.scales[ok]) == 0
+    assert np.array_equal(got[zero], ref_codes[zero])
+    differ = np.flatnonzero((got != ref_codes).any(axis=(1, 2)))
+    assert differ.size <= max(1, d_out // 4), differ
+
+
 def test_beam_search_refuses_before_launch():
     lay, w, h = _beam_inputs(30100, 8, 4096, 2)
     codes, cb, sc, _ = to_device(lay)
