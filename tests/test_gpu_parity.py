@@ -741,6 +741,50 @@ def test_backward_matches_oracle(d_out, d_in, M, n):
     _backward_check(lay, dy, dcb, ds)
 
 
+@pytest.mark.parametrize("d_out,d_in,M,n,codes", [
+    (264, 136, 1, 65, "any"),      # one row chunk and one group past a tile, one token past a stage
+    (256, 128, 2, 64, "one"),      # a whole tile and stage, every code the same: one list of 2048 pairs
+    (248, 1016, 4, 63, "skew"),    # short tiles; half of the codes equal
+    (776, 520, 8, 300, "any"),     # 20 tiles split over the tokens (one split shorter)
+    (2056, 3720, 2, 520, "any"),   # 270 tiles: a full round, then 14 tiles in two splits of the tokens
+    (72, 264, 5, 1, "skew"),
+])
+def test_backward_tiles_splits_and_code_skew(d_out, d_in, M, n, codes):
+    print(f"[backward] d_out={d_out} d_in={d_in} M={M} n={n} codes={codes}", flush=True)
+    rng = np.random.default_rng(20300 + d_out + n)
+    lay = synth.layer(20301 + d_out + d_in + M, d_out, d_in, M, 8, n=n)
+    if codes == "one":
+        lay.codes[:] = 77
+    elif codes == "skew":
+        lay.codes[rng.random(lay.codes.shape) < 0.5] = 255
+    dy = rng.standard_normal((n, d_out)).astype(np.float16)
+    c, cb, sc, x = to_device(lay)
+    dcb, ds = aq().backward(c, cb, sc, x, torch.from_numpy(dy).cuda())
+    torch.cuda.synchronize()
+    _backward_check(lay, dy, dcb, ds)
+    used = np.zeros((M, 256), dtype=bool)
+    for m in range(M):
+        used[m, lay.codes[:, :, m]] = True
+    assert not dcb.cpu().numpy()[~used].any()  # entries no code uses get nothing
+
+
+def test_backward_nonfinite_stays_with_its_codes():
+    """An infinite upstream gradient reaches the entries its row's codes use
+    and no others."""
+    lay = synth.layer(20400, 264, 256, 2, 8, n=70)
+    lay.codes[5, :, :] = 200
+    others = np.delete(np.arange(264), 5)
+    lay.codes[others] = np.minimum(lay.codes[others], 199)
+    dy = np.random.default_rng(20401).standard_normal((70, 264)).astype(np.float16)
+    dy[3, 5] = np.inf
+    c, cb, sc, x = to_device(lay)
+    dcb, ds = aq().backward(c, cb, sc, x, torch.from_numpy(dy).cuda())
+    torch.cuda.synchronize()
+    dcb, ds = dcb.cpu().numpy(), ds.cpu().numpy()
+    assert not np.isfinite(dcb[:, 200]).any() and not np.isfinite(ds[5])
+    assert np.isfinite(dcb[:, :200]).all() and np.isfinite(ds[others]).all()
+
+
 def test_backward_accumulates_and_cancelling():
     """Two calls add up (micro-batch accumulation); codebooks that cancel in
     pairs give the same gradients as the oracle."""
