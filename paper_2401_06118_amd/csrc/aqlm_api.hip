@@ -147,9 +147,9 @@ struct AnyLayer {
 // prefill kernel's is flat from 17 to 256 tokens at about four times that).
 constexpr int64_t kSmallBatchMax = 16;
 constexpr int64_t kChunkedMax = 64;
-// 1x16 takes the general tiled kernel per chunk, whose time grows faster
-// with the token count: chunks pay off up to two of them.
-constexpr int64_t kChunkedMax16 = 32;
+// Wide codes run in launches of up to 64 rows (2x12: 32) whose time barely
+// grows with the row count: chunks pay off up to this many rows.
+constexpr int64_t kChunkedMaxWide = 128;
 
 // Rows from which two wide codebooks take the prefill kernel.
 constexpr int64_t kPrefillMin2x12 = 192;
@@ -181,7 +181,13 @@ int check_tokens(const uint16_t* x, uint16_t* y, int64_t n, int64_t d_in) {
 // Llama-2-7B and 70B launch and on a 65536 x 8192 layer it was no faster (4-7 %
 // slower where a table is shared by 224-256 rows, 1.4-3x slower with fewer),
 // so it runs only when a caller asks for it (aqlm_gemv_grouped_path).
+// Wide codes whose rows are not multiples of 16 bytes take the small-batch
+// kernel for wide codes, which loads whole slots at any alignment and keeps its
+// gathers ahead across K-slices (1x16 9000 x 7304 67 -> 46 us, 2x12 54 -> 27,
+// 2x16 104 -> 85; the matrix-vector kernel loads such rows byte by byte).
 hipError_t gemv_dispatch(const aqlm::Layer& L, const uint16_t* x, uint16_t* y, hipStream_t s) {
+  if (L.B > 8 && !L.vec_codes && aqlm::gemm_wide_supported(L, 1))
+    return aqlm::launch_gemm_wide(L, 1, x, y, s);
   if (aqlm::gemv_mfma_supported(L.M, L.B) && aqlm::gemv_mfma_fits(&L, 1))
     return aqlm::launch_gemv_mfma(&L, &x, &y, 1, s);
   return aqlm::launch_gemv(L, x, y, s);
@@ -253,11 +259,15 @@ int gemm_dispatch(const aqlm::Layer& L, int64_t n, const uint16_t* x, uint16_t* 
   // 2..16 tokens with M = 2 or 4 8-bit codebooks: the matrix-vector kernel's
   // scheme with one MFMA column per token; otherwise the tiled kernel.
   if (aqlm::gemm_nb_supported(L, (int32_t)n)) return status_of(aqlm::launch_gemm_nb(L, (int32_t)n, x, y, s));
+  // Codes wider than 8 bits: up to 64 (2x12: 32) rows share each gathered
+  // codeword.
+  if (aqlm::gemm_wide_supported(L, (int32_t)n)) return status_of(aqlm::launch_gemm_wide(L, (int32_t)n, x, y, s));
   const bool chunk_nb = n <= kChunkedMax && aqlm::gemm_nb_supported(L, (int32_t)kSmallBatchMax);
-  const bool chunk_16 = n <= kChunkedMax16 && L.B > 8 && aqlm::mfma_supported(L);
-  if (n > kSmallBatchMax && (chunk_nb || chunk_16)) {
-    for (int64_t t0 = 0; t0 < n; t0 += kSmallBatchMax) {
-      const int64_t nt = n - t0 < kSmallBatchMax ? n - t0 : kSmallBatchMax;
+  const bool chunk_wide = n <= kChunkedMaxWide && aqlm::gemm_wide_supported(L, 2);
+  if (n > kSmallBatchMax && (chunk_nb || chunk_wide)) {
+    const int64_t chunk = chunk_nb ? kSmallBatchMax : aqlm::gemm_wide_rows(L);
+    for (int64_t t0 = 0; t0 < n; t0 += chunk) {
+      const int64_t nt = n - t0 < chunk ? n - t0 : chunk;
       const int st = gemm_dispatch(L, nt, x + t0 * d_in, y + t0 * d_out, s);
       if (st != AQLM_OK) return st;
     }

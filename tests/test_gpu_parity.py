@@ -810,6 +810,33 @@ def test_backward_refuses_before_launch():
         aq().backward(c16, cb16, sc16, x16, dy)
 
 
+# ------------------------------------------- small batch over wide codes
+
+@pytest.mark.parametrize("d_out,d_in,M,B,n", [
+    (1, 64, 1, 16, 1),          # one row of exactly one 16-byte slot, batch 1
+    (17, 72, 1, 15, 2),         # a last slot with one code; one row past a block
+    (300, 1040, 1, 16, 16),     # ragged rows of codes, two rounds
+    (300, 1040, 1, 16, 17),     # one row past a token block
+    (257, 2056, 2, 16, 33),     # the 64-row variant; two row blocks for some workgroups
+    (4100, 264, 1, 15, 64),     # rows just past one per 16 and CU
+    (9000, 136, 2, 15, 65),     # three row blocks, a second launch of one row
+    (16400, 96, 1, 16, 5),      # five blocks per CU: two rounds of workgroups
+    (530, 4104, 2, 12, 32),     # codebooks in LDS, a whole launch
+    (200, 72, 2, 12, 33),       # ... and one row more
+    (33, 8, 2, 12, 128),        # rows shorter than a slot (general kernel)
+    (64, 520, 2, 16, 128),
+])
+def test_gemm_wide_codes_shapes(d_out, d_in, M, B, n):
+    print(f"[wide] d_out={d_out} d_in={d_in} M={M} B={B} n={n}", flush=True)
+    lay = synth.layer(32000 + d_out + d_in + n, d_out, d_in, M, B, n=n)
+    codes, cb, sc, x = to_device(lay)
+    y = aq().gemm_small_batch(codes, cb, sc, x)
+    again = aq().gemm_small_batch(codes, cb, sc, x)
+    torch.cuda.synchronize()
+    assert torch.equal(y.view(torch.int16), again.view(torch.int16))
+    check_products(lay, fp16_to_np(y))
+
+
 # ----------------------------------------------------- Phase 1: beam search
 
 BEAM_CASES = [
