@@ -4,7 +4,7 @@
 // chunks of 8 inputs, each chunk a 16-byte slice of the codeword.
 //
 // These formats have no GPU speed figure in the paper (its GPU kernels cover
-// 1x16 and 2x8); the kernels here are plain vector-ALU ones:
+// 1x16 and 2x8):
 //   k_dequant_groups  one thread per 8-input chunk, codeword chunks gathered
 //                     from L2 (up to 512 KiB of codebooks), fp32 sums in
 //                     ascending m, one product with the scale, one rounding;
@@ -12,8 +12,10 @@
 //                     chunks of its input chunks in fp32 and multiplies them
 //                     with x; a fixed-order wave sum, the scale, one rounding.
 //                     The codebooks sit in LDS (one copy) when they fit
-//                     (up to 128 KiB: 4x8 gs16 32 KiB, 8x8 gs32 128 KiB),
-//                     else are gathered from L2 (15x8 gs64, 480 KiB).
+//                     (up to 128 KiB), else are gathered from L2 (15x8 gs64,
+//                     480 KiB);
+//   k_gemv_groups_mfma  batch 1 where the codebooks fit in LDS, M divides 16
+//                     and x fits beside them (4x8 gs16, 8x8 gs32): matrix cores.
 #include "common.h"
 #include "groups.h"
 #include "launch.h"
@@ -105,6 +107,190 @@ __global__ __launch_bounds__(kGrpThreads) void k_gemv_groups(const GroupLayer L,
   }
 }
 
+// Batch 1 on the matrix cores.  A 16-byte chunk of a codeword is a lane's A
+// fragment of v_mfma_f32_16x16x32_f16 (lane = row + 16 * slot), the matching
+// chunk of x column 0 of B; a code takes G8 of them.  An item is 16 rows x 64
+// code bytes: a lane's 16 codes (one 16-byte load at any alignment) are 16 / M
+// whole groups.  Items go round-robin to the 16 waves of a workgroup, code
+// loads two items ahead; a wave's sums move to LDS when its row block changes
+// and are added over the waves in a fixed order.  Bound by the LDS gathers (16
+// bytes per code chunk from kCopies codebook copies, lane l reads copy
+// l % kCopies): 11008 x 4096 4x8 gs16 44 -> 14 us, 8x8 gs32 67 -> 23 us against
+// one wave per row with byte loads of the codes and vector-ALU sums.
+// A row's last, partial slot loads the row's last 16 bytes and skips the codes
+// of the slot before; slots past the end read the row's first bytes against
+// x = 0.
+constexpr int kGmMaxRows = 128;  // rows per workgroup (8 blocks)
+
+template <int M, int G8>
+struct GmCfg {
+  static constexpr int kFit = 32 / (M * G8);  // copies that fit in 128 KiB (one copy: 4 KiB * M * G8)
+  static constexpr int kCopies = kFit >= 16 ? 16 : (kFit >= 8 ? 8 : (kFit >= 4 ? 4 : (kFit >= 2 ? 2 : 1)));
+  static constexpr size_t kCb = (size_t)M * 256 * G8 * kCopies * 16;
+};
+
+typedef uint32_t u32x4a1_t __attribute__((ext_vector_type(4), aligned(1)));
+
+template <int M, int G8>
+__global__ __launch_bounds__(kGrpThreads) void k_gemv_groups_mfma(const GroupLayer L, const uint4* __restrict__ x,
+                                                                  uint16_t* __restrict__ y, int32_t rows_per_wg) {
+  using C = GmCfg<M, G8>;
+  constexpr int kCopies = C::kCopies, kGroups = 16 / M;  // whole groups per lane slot
+  extern __shared__ uint4 lds[];
+  uint4* const cb_lds = lds;  // [chunk][M][256][copies]
+  uint4* const x_lds = lds + C::kCb / 16;
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int r16 = lane & 15, slot = lane >> 4;
+  const int32_t row0 = (int32_t)blockIdx.x * rows_per_wg;
+  const int32_t rows = L.d_out - row0 < rows_per_wg ? L.d_out - row0 : rows_per_wg;
+  const int32_t G = L.d_in / (8 * G8);
+  const uint32_t pitch = (uint32_t)G * M;  // code bytes per row (at least 16)
+  const int KS = (int)((pitch + 63u) / 64u);
+  const int items = (rows + 15) / 16 * KS;
+  const int xc = KS * 4 * kGroups * G8;    // x chunks staged, zero past the end
+  const uint4* __restrict__ cb = reinterpret_cast<const uint4*>(L.codebooks);
+  float* const part = reinterpret_cast<float*>(x_lds + xc);
+
+  // this lane's slot of an item, and how many codes it starts before the slot
+  auto slot_off = [&](int ks, int& back) -> uint32_t {
+    const uint32_t off = (uint32_t)ks * 64u + (uint32_t)slot * 16u;
+    back = 0;
+    if (off >= pitch) return 0u;
+    if (off + 16u > pitch) {
+      back = (int)(off + 16u - pitch);
+      return pitch - 16u;
+    }
+    return off;
+  };
+  auto load_codes = [&](int item, u32x4_t& w) {
+    const int it = item < items ? item : items - 1;
+    int back;
+    int row = it / KS * 16 + r16;
+    row = row < rows ? row : rows - 1;
+    const uint8_t* p = L.codes + (size_t)(row0 + row) * pitch + slot_off(it % KS, back);
+    w = __builtin_nontemporal_load(reinterpret_cast<const u32x4a1_t*>(p));
+  };
+
+  // small loads first, then the first items' codes
+  constexpr int kCbLoads = M * 256 * G8 / kGrpThreads > 0 ? M * 256 * G8 / kGrpThreads : 1;
+  uint4 cbv[kCbLoads];
+#pragma unroll
+  for (int i = 0; i < kCbLoads; ++i)
+    if (tid + i * kGrpThreads < M * 256 * G8) cbv[i] = cb[tid + i * kGrpThreads];
+  u32x4_t cw[2];
+  load_codes(wave, cw[0]);
+  load_codes(wave + kGrpWaves, cw[1]);
+  const float sc = h2f(L.scales[row0 + (tid < rows ? tid : rows - 1)]);
+  for (int e = tid; e < xc; e += kGrpThreads) x_lds[e] = e < G * G8 ? x[e] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+  for (int i = 0; i < kCbLoads; ++i) {
+    const int q = tid + i * kGrpThreads;
+    if (q < M * 256 * G8) {
+#pragma unroll
+      for (int c = 0; c < kCopies; ++c)
+        cb_lds[((q % G8) * M * 256 + q / G8) * kCopies + ((c + lane) % kCopies)] = cbv[i];
+    }
+  }
+  for (int e = tid; e < (rows + 15) / 16 * kGrpWaves * 16; e += kGrpThreads) part[e] = 0.f;
+  __syncthreads();
+
+  f4_t acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+  int cur = -1;
+  auto flush = [&]() {
+    if (cur >= 0 && r16 == 0) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) part[(cur * kGrpWaves + wave) * 16 + 4 * slot + e] = acc0[e] + acc1[e];
+    }
+  };
+  const uint4* const my_cb = cb_lds + lane % kCopies;
+  for (int item = wave, u = 0; item < items; item += kGrpWaves, u ^= 1) {
+    const u32x4_t w = u ? cw[1] : cw[0];
+    // (the codes two items on: a select keeps both sets in registers)
+    u32x4_t nw;
+    load_codes(item + 2 * kGrpWaves, nw);
+    const int rb = item / KS, ks = item % KS;
+    if (rb != cur) {
+      flush();
+      acc0 = acc1 = f4_t{0.f, 0.f, 0.f, 0.f};
+      cur = rb;
+    }
+    int back;
+    slot_off(ks, back);
+    // first chunk of the group of this lane's code 0
+    const int c0 = ((ks * 4 + slot) * kGroups - back / M) * G8;
+#pragma unroll
+    for (int q = 0; q < kGroups; ++q) {
+      const bool use = r16 == 0 && q * M >= back;
+#pragma unroll
+      for (int p = 0; p < G8; ++p) {
+        uint4 xb = make_uint4(0, 0, 0, 0);
+        if (use) xb = x_lds[c0 + q * G8 + p];
+        const h8_t xh = __builtin_bit_cast(h8_t, xb);
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+          const int t = q * M + m;
+          const uint32_t code = (w[t / 4] >> (8 * (t % 4))) & 0xFFu;
+          const uint4 av = my_cb[((p * M + m) * 256 + code) * kCopies];
+          f4_t& a = (m + p) % 2 == 0 ? acc0 : acc1;
+          a = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8_t, av), xh, a, 0, 0, 0);
+        }
+      }
+    }
+    if (u)
+      cw[1] = nw;
+    else
+      cw[0] = nw;
+  }
+  flush();
+  __syncthreads();
+  if (tid < rows) {
+    float s = 0.f;
+#pragma unroll
+    for (int v = 0; v < kGrpWaves; ++v) s += part[(tid / 16 * kGrpWaves + v) * 16 + tid % 16];
+    y[row0 + tid] = f2h(sc * s);
+  }
+}
+
+template <int M, int G8>
+size_t gm_lds(const GroupLayer& L, int rows) {
+  const size_t KS = ((size_t)(L.d_in / L.g) * M + 63) / 64;
+  return GmCfg<M, G8>::kCb + KS * 4 * (16 / M) * G8 * 16 + (size_t)((rows + 15) / 16) * kGrpWaves * 64;
+}
+
+// Launches the matrix-core kernel if it takes the layer.
+template <int M, int G8>
+bool try_groups_mfma(const GroupLayer& L, const uint16_t* x, uint16_t* y, hipStream_t s, hipError_t* e) {
+  if constexpr (M * G8 > 32) {
+    return false;
+  } else {
+    if ((int64_t)(L.d_in / L.g) * M < 16) return false;
+    // rows split evenly over whole rounds of one workgroup per CU
+    const int64_t cus = num_cus(), rounds = (L.d_out + kGmMaxRows * cus - 1) / (kGmMaxRows * cus);
+    const int rows = (int)((L.d_out + rounds * cus - 1) / (rounds * cus));
+    const size_t lds = gm_lds<M, G8>(L, rows);
+    if (lds > 160 * 1024) return false;
+    auto kern = k_gemv_groups_mfma<M, G8>;
+    *e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), 160 * 1024);
+    if (*e != hipSuccess) return true;
+    hipLaunchKernelGGL(kern, dim3((uint32_t)((L.d_out + rows - 1) / rows)), dim3(kGrpThreads), lds, s, L,
+                       reinterpret_cast<const uint4*>(x), y, rows);
+    *e = hipGetLastError();
+    return true;
+  }
+}
+
+template <int M>
+bool try_groups_mfma_g(const GroupLayer& L, const uint16_t* x, uint16_t* y, hipStream_t s, hipError_t* e) {
+  switch (L.g) {
+    case 16: return try_groups_mfma<M, 2>(L, x, y, s, e);
+    case 32: return try_groups_mfma<M, 4>(L, x, y, s, e);
+    case 64: return try_groups_mfma<M, 8>(L, x, y, s, e);
+  }
+  return false;
+}
+
 }  // namespace
 
 hipError_t launch_dequant_groups(const GroupLayer& L, uint16_t* w, hipStream_t s) {
@@ -117,6 +303,16 @@ hipError_t launch_dequant_groups(const GroupLayer& L, uint16_t* w, hipStream_t s
 }
 
 hipError_t launch_gemv_groups(const GroupLayer& L, const uint16_t* x, uint16_t* y, hipStream_t s) {
+  hipError_t me = hipSuccess;
+  bool taken = false;
+  switch (L.M) {
+    case 1: taken = try_groups_mfma_g<1>(L, x, y, s, &me); break;
+    case 2: taken = try_groups_mfma_g<2>(L, x, y, s, &me); break;
+    case 4: taken = try_groups_mfma_g<4>(L, x, y, s, &me); break;
+    case 8: taken = try_groups_mfma_g<8>(L, x, y, s, &me); break;
+    case 16: taken = try_groups_mfma_g<16>(L, x, y, s, &me); break;
+  }
+  if (taken) return me;
   const size_t cb_bytes = (size_t)L.M * 256 * (size_t)L.g * 2;
   const int32_t row_blocks = (L.d_out + kGrpWaves - 1) / kGrpWaves;
   int32_t grid = num_cus();

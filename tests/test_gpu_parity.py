@@ -810,6 +810,34 @@ def test_backward_refuses_before_launch():
         aq().backward(c16, cb16, sc16, x16, dy)
 
 
+# ------------------------------------- larger groups on the matrix cores
+
+@pytest.mark.parametrize("d_out,d_in,M,g", [
+    # (one block of rows of exactly one slot; not a single row: the reference
+    # rounds its weights to fp16, an absolute error of up to 2^-11 * sum |w x|,
+    # and one output that cancels has no bound relative to itself)
+    (16, 64, 4, 16),
+    (17, 80, 4, 16),        # a last slot with one group
+    (300, 1040, 2, 16),     # ragged rows, fewer items than waves
+    (33, 4128, 1, 64),      # more chunks than codes
+    (4097, 352, 8, 32),     # one copy of the codebooks, rows just past one per 16 and CU
+    (9000, 48, 16, 16),
+    (33000, 32, 8, 16),     # two rounds of workgroups
+    (40, 96, 3, 32),        # M that does not divide 16 (vector kernel)
+    (40, 20480, 8, 32),     # x too large beside the codebooks (vector kernel)
+])
+def test_gemv_groups_shapes(d_out, d_in, M, g):
+    print(f"[groups] d_out={d_out} d_in={d_in} M={M} g={g}", flush=True)
+    d_in = d_in // g * g
+    lay = synth.layer(33000 + d_out + d_in + M, d_out, d_in, M, 8, g=g)
+    codes, cb, sc, x = to_device(lay)
+    y = aq().gemv(codes, cb, sc, x[0])
+    again = aq().gemv(codes, cb, sc, x[0])
+    torch.cuda.synchronize()
+    assert torch.equal(y.view(torch.int16), again.view(torch.int16))
+    check_products(lay, fp16_to_np(y)[None, :])
+
+
 # ------------------------------------------- small batch over wide codes
 
 @pytest.mark.parametrize("d_out,d_in,M,B,n", [
