@@ -125,20 +125,48 @@ __device__ __forceinline__ void gf_mfma(const h8_t (&xf)[FM], const h8_t (&wf)[F
 // wait for every load in flight before the first read.  Ordering across
 // intervals is the explicit waits and the barrier of the caller, and the
 // scheduling barriers keep the phases in the order above.
-template <int FM, int FN, int PER>
+//
+// MIX (8-wave shapes): within each phase the LDS reads, the loads and the MFMAs
+// alternate, so that the matrix cores do not idle while a wave issues its
+// reads and the LDS sees them spread out (reads and stage writes together take
+// about as many LDS clocks as the MFMAs take).  Same box, against all reads of a
+// phase before its MFMAs: 2048 x 11008 x 4096 178 -> 169 us, 2048 x 8192 x 4096
+// 117 -> 113, 1024 x 11008 x 4096 83 -> 79, 333 x 4096 x 11008 48 -> 45.  With 16
+// waves of 64 x 32 it is slower (512 x 11008 x 4096 53 -> 53, 2048 x 11008 182 ->
+// 188): there the other waves fill the gaps.  256 x 256 with 4 waves of 128 x
+// 128 spills (262 us and more).
+template <int FM, int FN, int PER, bool MIX>
 __device__ __forceinline__ void gf_interval(const uint4* __restrict__ rd, uint4* __restrict__ wr,
                                             const uint4* const* src, int kc, int first_inst, int xr0, int wr0,
                                             int slot, f4_t (&acc)[FM][FN], h8_t (&xa)[FM], h8_t (&wa)[FN]) {
+  // (scheduling groups: 0x8 MFMA, 0x20 global loads, 0x100 LDS reads)
+  constexpr int kRun = FM * FN / (FM + FN);  // MFMAs after each read
 #pragma unroll
   for (int i = 0; i < PER; ++i) load_to_lds(src[i] + kc, wr + (first_inst + i) * 64);
   h8_t xb[FM], wb[FN];
   gf_read_half<FM, FN>(rd, 0, xr0, wr0, slot, xb, wb);
-  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (!MIX) __builtin_amdgcn_sched_barrier(0);
   gf_mfma<FM, FN>(xa, wa, acc);
+  if constexpr (MIX) {
+#pragma unroll
+    for (int i = 0; i < FM + FN; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      if (i < PER) __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x8, kRun, 0);
+    }
+  }
   __builtin_amdgcn_sched_barrier(0);
   gf_read_half<FM, FN>(rd, 1, xr0, wr0, slot, xa, wa);
-  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (!MIX) __builtin_amdgcn_sched_barrier(0);
   gf_mfma<FM, FN>(xb, wb, acc);
+  if constexpr (MIX) {
+#pragma unroll
+    for (int i = 0; i < FM + FN; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x8, kRun, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
 }
 
 // Waits until none of this wave's LDS reads is in flight.
@@ -221,7 +249,7 @@ __global__ __launch_bounds__(WM * WN * kWave) void k_gemm_f16(const GemmF16Args 
   // (one call site for every interval, so that all share the alias scopes)
   for (int k = 0; k < ksteps; ++k) {
     const int kn = k + S - 1;
-    gf_interval<FM, FN, PER>(lds + (k % S) * P::kStageU4, lds + (kn % S) * P::kStageU4, src,
+    gf_interval<FM, FN, PER, (P::kWaves <= 8)>(lds + (k % S) * P::kStageU4, lds + (kn % S) * P::kStageU4, src,
                              (kn < ksteps ? kn : ksteps - 1) * (kGfK / 8), wave * PER, xr0, wr0, slot, acc, xa, wa);
     wait_loads<PER * (S - 2)>();
     wait_lds_reads();
