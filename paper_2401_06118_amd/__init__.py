@@ -46,8 +46,17 @@ __all__ = ["dequantize", "gemv", "gemv_grouped", "gemm_small_batch", "gemm_works
            "status_string", "layer_args", "packed_layer_args"]
 
 
+# The current stream's handle without building a torch.cuda.Stream (0.1 us
+# against 2.7 us, a quarter of a small call's host time) where this torch has
+# the two accessors.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream_handle(stream) -> int:
     if stream is None:
+        if _raw_stream is not None and _current_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_current_device())
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream)
 

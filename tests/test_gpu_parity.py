@@ -810,6 +810,30 @@ def test_backward_refuses_before_launch():
         aq().backward(c16, cb16, sc16, x16, dy)
 
 
+def test_calls_follow_the_current_stream():
+    """The default stream argument is the current stream: inside a stream
+    context and under capture too."""
+    lay = synth.layer(32900, 64, 512, 2, 8)
+    codes, cb, sc, x = to_device(lay)
+    ref = aq().gemv(codes, cb, sc, x[0])
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert aq()._stream_handle(None) == side.cuda_stream
+        y = aq().gemv(codes, cb, sc, x[0])
+    side.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        assert aq()._stream_handle(None) == torch.cuda.current_stream().cuda_stream
+        yg = aq().gemv(codes, cb, sc, x[0])
+    for _ in range(3):
+        yg.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(yg, ref)
+    assert torch.equal(y, ref)
+
+
 # ------------------------------------- larger groups on the matrix cores
 
 @pytest.mark.parametrize("d_out,d_in,M,g", [
