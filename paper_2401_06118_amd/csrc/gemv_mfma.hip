@@ -394,6 +394,7 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
   if constexpr (STEP) __syncthreads();
 
   // 1. codebooks, x and scales first (they retire before the code stream).
+  constexpr bool kPairCb = COPIES == 8 && M == 2;
   uint4 cbv = make_uint4(0, 0, 0, 0);
   if (tid < M * 256) cbv = cb[tid];
   // this thread's output row scale, needed only at the end (an unconditional
@@ -457,12 +458,13 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
 
   // (the step kernel: codebooks to LDS while waiting, then x)
   auto stage_cb = [&]() {
-    constexpr bool kPair = COPIES == 8 && M == 2;
+    // (half of the waves write all copies: spreading them over all 16 waves
+    // made the 7B step 2.5 % slower)
     if (tid < M * 256) {
 #pragma unroll
       for (int k = 0; k < COPIES; ++k) {
         const int c = (k + lane) % COPIES;
-        cb_lds[kPair ? (tid & 255) * 16 + (tid >> 8) * 8 + c : tid * COPIES + c] = cbv;
+        cb_lds[kPairCb ? (tid & 255) * 16 + (tid >> 8) * 8 + c : tid * COPIES + c] = cbv;
       }
     }
   };
@@ -472,14 +474,12 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
     load_x();
   }
 
-  // 3. stage codebook copies and x.  Eight copies of two codebooks (x too
-  // large for sixteen) are interleaved per codeword: entry e holds the 8
-  // copies of codebook 0, then the 8 of codebook 1 (256 bytes, every 16-byte
+  // 3. stage codebook copies and x.  Eight copies of two codebooks are
+  // interleaved per codeword: entry e holds the 8 copies of codebook 0, then the 8 of codebook 1 (256 bytes, every 16-byte
   // bank group once).  Lanes 8-15 of each 16-lane group then gather the
   // other code of the group (same x, other codebook) in the same
   // instruction, so the 16 lanes of one LDS pass read 16 different bank
   // groups; each row still gets both codebooks over the pair of MFMAs.
-  constexpr bool kPairCb = COPIES == 8 && M == 2;
   if constexpr (!STEP) stage_cb();
 #pragma unroll
   for (int i = 0; i < C::kXL; ++i) {
@@ -1004,9 +1004,8 @@ hipError_t launch_copies(const GemvBatch& bt, int pf, size_t lds_bytes, hipStrea
 // (M = 2, 8-bit codes, 16-byte code rows) body instantiations: (id, copies,
 // row blocks, ring depth)
 #define AQLM_STEP_VARIANTS(X)                                                                    \
-  X(0, 16, 1, 1) X(1, 16, 1, 2) X(2, 16, 1, 4) X(3, 16, 1, 8) X(4, 16, 2, 2) X(6, 16, 3, 1)       \
-  X(7, 16, 4, 1) X(8, 16, 4, 2) X(9, 16, 5, 1) X(10, 16, 6, 1) X(11, 16, 7, 1) X(12, 8, 1, 1)      \
-  X(13, 8, 1, 2) X(14, 8, 1, 4) X(15, 8, 1, 8) X(16, 8, 2, 2)
+  X(0, 8, 1, 1) X(1, 8, 1, 2) X(2, 8, 1, 4) X(3, 8, 1, 8) X(4, 8, 2, 2) X(5, 8, 3, 1)             \
+  X(6, 8, 4, 1) X(7, 8, 4, 2) X(8, 8, 5, 1) X(9, 8, 6, 1) X(10, 8, 7, 1)
 
 int step_variant(int M, int copies, int rb, int d, bool vec) {
   if (M != 2 || !vec) return -1;
@@ -1289,9 +1288,12 @@ hipError_t gemv_mfma_impl(const Layer* Ls, const uint16_t* const* xs, uint16_t* 
 #undef AQLM_GEMV_L2
     return hipErrorInvalidValue;
   }
-  // the most codebook copies that fit next to x and the partials
+  // The most codebook copies that fit next to x and the partials; for two
+  // codebooks eight, interleaved (conflict-free like sixteen, and half of the
+  // staging: Llama-2-7B decode over tiled codes 211 -> 203 us per 8 blocks, 70B
+  // 195 -> 193 per 3 blocks, same box), which fit beside every x.
   const size_t per_copy = (size_t)M * 256 * 16;
-  int copies = 16;
+  int copies = M == 2 ? 8 : 16;
   while (copies > 1 && base + per_copy * copies > limit) copies /= 2;
   if (base + per_copy * copies > limit) return hipErrorInvalidValue;
   const size_t lds = base + per_copy * copies;
@@ -1301,22 +1303,22 @@ hipError_t gemv_mfma_impl(const Layer* Ls, const uint16_t* const* xs, uint16_t* 
     plan->lds_bytes = (int32_t)lds;
     return plan->variant < 0 ? hipErrorInvalidValue : hipSuccess;
   }
-#define AQLM_GEMV_COPIES(MM)                                                                     \
-  switch (copies) {                                                                              \
-    case 16: return vec ? launch_ks_rb<MM, 16, true>(bt, rb_max, nks_min, lds, s)                        \
-                        : launch_ks_rb<MM, 16, false>(bt, rb_max, nks_min, lds, s);                      \
-    case 8: return vec ? launch_ks_rb<MM, 8, true>(bt, rb_max, nks_min, lds, s)                          \
-                       : launch_ks_rb<MM, 8, false>(bt, rb_max, nks_min, lds, s);                        \
-    case 4: return vec ? launch_ks_rb<MM, 4, true>(bt, rb_max, nks_min, lds, s)                          \
-                       : launch_ks_rb<MM, 4, false>(bt, rb_max, nks_min, lds, s);                        \
-    default: return hipErrorInvalidValue;                                                        \
+#define AQLM_GEMV_KS(MM, C)                                           \
+  return vec ? launch_ks_rb<MM, C, true>(bt, rb_max, nks_min, lds, s) \
+             : launch_ks_rb<MM, C, false>(bt, rb_max, nks_min, lds, s);
+  if (M == 2) {
+    if (copies == 8) AQLM_GEMV_KS(2, 8)
+    return hipErrorInvalidValue;
   }
-  switch (M) {
-    case 1: AQLM_GEMV_COPIES(1)
-    case 2: AQLM_GEMV_COPIES(2)
-    case 4: AQLM_GEMV_COPIES(4)
+  switch (M * 16 + copies) {
+    case 1 * 16 + 16: AQLM_GEMV_KS(1, 16)
+    case 1 * 16 + 8: AQLM_GEMV_KS(1, 8)
+    case 1 * 16 + 4: AQLM_GEMV_KS(1, 4)
+    case 4 * 16 + 16: AQLM_GEMV_KS(4, 16)
+    case 4 * 16 + 8: AQLM_GEMV_KS(4, 8)
+    case 4 * 16 + 4: AQLM_GEMV_KS(4, 4)
   }
-#undef AQLM_GEMV_COPIES
+#undef AQLM_GEMV_KS
   return hipErrorInvalidValue;
 }
 
