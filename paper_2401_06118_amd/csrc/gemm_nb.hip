@@ -96,8 +96,8 @@ __global__ __launch_bounds__(kThreadsNB) void k_gemm_nb(const GemmNbArgs a) {
   const uint32_t k_limit = tiled ? 0xFFFFFFFFu : pitch;  // (tiles hold whole K-slices)
 
   uint4* cb_lds = lds;
-  uint4* x_lds = lds + M * 256 * COPIES;                        // [n][kXG]
-  float* part = reinterpret_cast<float*>(x_lds + n * kXG);      // [wave][16 rows][16 tokens]
+  uint4* x_lds = lds + M * 256 * COPIES;             // [n][kXG]
+  float* part = reinterpret_cast<float*>(x_lds);     // [wave][16 rows][16 tokens], once x has been read
 
   // 1. small loads first: codebooks, the scales of this thread's epilogue
   // rows (clamped, unconditional), x of round 0.
@@ -149,17 +149,36 @@ __global__ __launch_bounds__(kThreadsNB) void k_gemm_nb(const GemmNbArgs a) {
   for (int i = 0; i < kAhead; ++i)
     if (i / RB < nks) issue_rb(i / RB, i % RB, ring[i / RB][i % RB]);
 
-  // 3. codebook copies (lane l reads copy l % COPIES).
+  // 3. codebook copies (lane l reads copy l % COPIES).  16 / M copies are
+  // interleaved per codeword index: entry e is 256 bytes, the copies of
+  // codebook 0, then those of codebook 1, ...  In each MFMA the lanes of a row
+  // of 16 take the M codes of a group in M different orders (code t ^ flip;
+  // all multiply the same x slice, so every row still gets each code once), and
+  // the 16 lanes read 16 different 16-byte bank groups: no conflicts.
+  constexpr bool kMix = M * COPIES == 16;
   if (tid < M * 256) {
 #pragma unroll
-    for (int k = 0; k < COPIES; ++k) cb_lds[tid * COPIES + ((k + lane) % COPIES)] = cbv;
+    for (int k = 0; k < COPIES; ++k) {
+      const int c = (k + lane) % COPIES;
+      cb_lds[kMix ? (tid & 255) * 16 + (tid >> 8) * COPIES + c : tid * COPIES + c] = cbv;
+    }
   }
 
   const uint32_t copy_off = (uint32_t)(lane % COPIES) * 16u;
   const uint32_t cb_base = (uint32_t)(uintptr_t)cb_lds;
-  uint32_t base_m[M];
+  // address of code t of the lane's slot: byte t ^ flip of its code words
+  const uint32_t flip = kMix ? (uint32_t)(r16 / COPIES) : 0u;
+  uint32_t base_m[M], psel[4];
 #pragma unroll
-  for (int m = 0; m < M; ++m) base_m[m] = cb_base + ((uint32_t)m << 16) + copy_off;
+  for (int m = 0; m < M; ++m)
+    base_m[m] = kMix ? cb_base + (((uint32_t)m ^ flip) * COPIES + (uint32_t)(lane % COPIES)) * 16u
+                     : cb_base + ((uint32_t)m << 16) + copy_off;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) psel[k] = 0x0C020000u | ((4u + ((uint32_t)k ^ flip)) << 8);
+  auto gaddr = [&](uint32_t word, int t) -> uint32_t {
+    if constexpr (kMix) return __builtin_amdgcn_perm(word, base_m[t % M], psel[t % 4]);
+    return cw_addr<M, COPIES>(word, t % 4, base_m[t % M], copy_off + cb_base, t % M);
+  };
   f4_t acc[RB];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) acc[rb] = f4_t{0.f, 0.f, 0.f, 0.f};
@@ -198,11 +217,8 @@ __global__ __launch_bounds__(kThreadsNB) void k_gemm_nb(const GemmNbArgs a) {
 #pragma unroll
             for (int u = 0; u < kStep; ++u) {
               const int t = t0 + u;
-              av[u] = lds_load16(
-                  cw_addr<M, COPIES>(ring[d][rb][t / 4], t % 4, base_m[t % M], copy_off + cb_base, t % M));
-              if (pair)
-                bv[u] = lds_load16(cw_addr<M, COPIES>(ring[d][pair ? rb + 1 : rb][t / 4], t % 4, base_m[t % M],
-                                                      copy_off + cb_base, t % M));
+              av[u] = lds_load16(gaddr(ring[d][rb][t / 4], t));
+              if (pair) bv[u] = lds_load16(gaddr(ring[d][pair ? rb + 1 : rb][t / 4], t));
             }
 #pragma unroll
             for (int u = 0; u < kStep; ++u) {
@@ -291,9 +307,10 @@ hipError_t launch_nb_rb(const GemmNbArgs& a, int nwg, int rb, int rounds, size_t
 template <int M, bool VEC>
 hipError_t launch_nb_copies(const GemmNbArgs& a, int nwg, int rb, int rounds, int copies, size_t lds,
                             hipStream_t s) {
+  if constexpr (M == 2) {
+    if (copies == 8) return launch_nb_rb<M, 8, VEC>(a, nwg, rb, rounds, lds, s);
+  }
   switch (copies) {
-    case 16: return launch_nb_rb<M, 16, VEC>(a, nwg, rb, rounds, lds, s);
-    case 8: return launch_nb_rb<M, 8, VEC>(a, nwg, rb, rounds, lds, s);
     case 4: return launch_nb_rb<M, 4, VEC>(a, nwg, rb, rounds, lds, s);
     case 2: return launch_nb_rb<M, 2, VEC>(a, nwg, rb, rounds, lds, s);
     case 1: return launch_nb_rb<M, 1, VEC>(a, nwg, rb, rounds, lds, s);
@@ -303,7 +320,8 @@ hipError_t launch_nb_copies(const GemmNbArgs& a, int nwg, int rb, int rounds, in
 
 template <int M>
 size_t nb_fixed_lds(int n) {
-  return (size_t)n * NbCfg<M>::kXG * 16 + NbCfg<M>::kPartBytes;
+  const size_t x = (size_t)n * NbCfg<M>::kXG * 16;
+  return x > NbCfg<M>::kPartBytes ? x : NbCfg<M>::kPartBytes;
 }
 
 size_t nb_fixed_lds_m(int M, int n) {
@@ -338,7 +356,10 @@ hipError_t launch_gemm_nb(const Layer& L, int32_t n, const uint16_t* x, uint16_t
   const int rounds = (KS + kWavesNB - 1) / kWavesNB;
   const size_t fixed = nb_fixed_lds_m(M, n);
   const size_t per_copy = (size_t)M * 256 * 16;
-  int copies = 16;
+  // the conflict-free interleaved layout where it fits, else as many copies as
+  // do (11008 x 4096 4x8 at 16 rows 17.2 -> 14.0 us, at 4
+  // 13.2 -> 11.7; 2x8 at 8 rows 13.7 -> 11.9; 4096 x 11008 4x8 at 16 22.2 -> 18.6)
+  int copies = 16 / M;
   while (copies > 1 && fixed + per_copy * copies > kLdsLimit) copies /= 2;
   const size_t lds = fixed + per_copy * copies;
   GemmNbArgs a{static_cast<const uint8_t*>(L.codes), reinterpret_cast<const uint4*>(L.codebooks), L.scales,

@@ -810,6 +810,21 @@ def test_backward_refuses_before_launch():
         aq().backward(c16, cb16, sc16, x16, dy)
 
 
+@pytest.mark.parametrize("M,n", [(2, 10), (2, 12), (2, 13), (2, 16), (4, 2), (4, 4), (4, 5), (4, 16)])
+def test_small_batch_copy_layouts(M, n):
+    """Row counts at which the codebook copies and their layout change (two
+    codebooks: eight interleaved up to 12 rows, then four; four codebooks: four
+    interleaved, the partial sums longer than x up to 4 rows), tiled and
+    row-major bit for bit."""
+    lay = synth.layer(32800 + M + n, 530, 1096, M, 8, n=n)
+    codes, cb, sc, x = to_device(lay)
+    y = aq().gemm_small_batch(codes, cb, sc, x)
+    yt = aq().TiledCodes(codes, cb, sc).gemm_small_batch(x)
+    torch.cuda.synchronize()
+    assert torch.equal(y.view(torch.int16), yt.view(torch.int16))
+    check_products(lay, fp16_to_np(y))
+
+
 def test_calls_follow_the_current_stream():
     """The default stream argument is the current stream: inside a stream
     context and under capture too."""
