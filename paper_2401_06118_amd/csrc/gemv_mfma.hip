@@ -394,7 +394,7 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
   if constexpr (STEP) __syncthreads();
 
   // 1. codebooks, x and scales first (they retire before the code stream).
-  constexpr bool kPairCb = COPIES == 8 && M == 2;
+  constexpr bool kPairCb = M >= 2 && M * COPIES == 16;
   uint4 cbv = make_uint4(0, 0, 0, 0);
   if (tid < M * 256) cbv = cb[tid];
   // this thread's output row scale, needed only at the end (an unconditional
@@ -464,7 +464,7 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
 #pragma unroll
       for (int k = 0; k < COPIES; ++k) {
         const int c = (k + lane) % COPIES;
-        cb_lds[kPairCb ? (tid & 255) * 16 + (tid >> 8) * 8 + c : tid * COPIES + c] = cbv;
+        cb_lds[kPairCb ? (tid & 255) * 16 + (tid >> 8) * COPIES + c : tid * COPIES + c] = cbv;
       }
     }
   };
@@ -474,12 +474,13 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
     load_x();
   }
 
-  // 3. stage codebook copies and x.  Eight copies of two codebooks are
-  // interleaved per codeword: entry e holds the 8 copies of codebook 0, then the 8 of codebook 1 (256 bytes, every 16-byte
-  // bank group once).  Lanes 8-15 of each 16-lane group then gather the
-  // other code of the group (same x, other codebook) in the same
-  // instruction, so the 16 lanes of one LDS pass read 16 different bank
-  // groups; each row still gets both codebooks over the pair of MFMAs.
+  // 3. stage codebook copies and x.  With two or four codebooks, 16 / M copies
+  // are interleaved per codeword index: entry e (256 bytes, every 16-byte bank
+  // group once) holds the copies of codebook 0, then those of codebook 1, ...
+  // The 16 lanes of a row group gather the M codes of a group (same x, other
+  // codebook) in M different orders, so the lanes of one LDS pass read 16
+  // different bank groups; each row still gets every codebook over the M
+  // MFMAs.
   if constexpr (!STEP) stage_cb();
 #pragma unroll
   for (int i = 0; i < C::kXL; ++i) {
@@ -494,16 +495,17 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
   uint32_t base_m[M];
 #pragma unroll
   for (int m = 0; m < M; ++m) base_m[m] = cb_base + ((uint32_t)m << 16) + copy_off;
-  // interleaved layout: address (code * 16 + m * 8 + copy) * 16, with m and
-  // the code byte (t ^ flip) flipped on lanes 8-15
-  const uint32_t flip = (uint32_t)(r16 >> 3);
-  uint32_t pbase[2], psel[4];
+  // interleaved layout: address (code * 16 + m * copies + copy) * 16, with m
+  // and the code byte t exchanged by t ^ flip in lane group `flip`
+  const uint32_t flip = kPairCb ? (uint32_t)(r16 / COPIES) : 0u;
+  uint32_t pbase[M], psel[4];
 #pragma unroll
-  for (int tm = 0; tm < 2; ++tm) pbase[tm] = cb_base + ((((uint32_t)tm ^ flip) * 8u + (uint32_t)(lane % 8)) * 16u);
+  for (int tm = 0; tm < M; ++tm)
+    pbase[tm] = cb_base + ((((uint32_t)tm ^ flip) * (uint32_t)COPIES + (uint32_t)(lane % COPIES)) * 16u);
 #pragma unroll
   for (int k = 0; k < 4; ++k) psel[k] = 0x0C020000u | ((4u + ((uint32_t)k ^ flip)) << 8);
   auto gaddr = [&](uint32_t word, int t) -> uint32_t {
-    if constexpr (kPairCb) return __builtin_amdgcn_perm(word, pbase[t % 2], psel[t % 4]);
+    if constexpr (kPairCb) return __builtin_amdgcn_perm(word, pbase[t % M], psel[t % 4]);
     return cw_addr<M, COPIES>(word, t % 4, base_m[t % M], copy_off + cb_base, t % M);
   };
   {
@@ -1288,12 +1290,15 @@ hipError_t gemv_mfma_impl(const Layer* Ls, const uint16_t* const* xs, uint16_t* 
 #undef AQLM_GEMV_L2
     return hipErrorInvalidValue;
   }
-  // The most codebook copies that fit next to x and the partials; for two
-  // codebooks eight, interleaved (conflict-free like sixteen, and half of the
-  // staging: Llama-2-7B decode over tiled codes 211 -> 203 us per 8 blocks, 70B
-  // 195 -> 193 per 3 blocks, same box), which fit beside every x.
+  // One codebook: the most copies that fit next to x and the partials.  Two and
+  // four: 16 / M copies, interleaved, which fit beside every x: two codebooks
+  // against sixteen copies (conflict-free too, twice the staging) Llama-2-7B
+  // decode over tiled codes 211 -> 203 us per 8 blocks, 70B 195 -> 193 per 3
+  // blocks; four against eight plain copies (bank conflicts) 11008 x 4096 at
+  // batch 1 10.7 -> 9.3 us, 4096 x 11008 11.7 -> 10.2 (same box each, the
+  // host side of the call included).
   const size_t per_copy = (size_t)M * 256 * 16;
-  int copies = M == 2 ? 8 : 16;
+  int copies = 16 / M;
   while (copies > 1 && base + per_copy * copies > limit) copies /= 2;
   if (base + per_copy * copies > limit) return hipErrorInvalidValue;
   const size_t lds = base + per_copy * copies;
@@ -1303,21 +1308,16 @@ hipError_t gemv_mfma_impl(const Layer* Ls, const uint16_t* const* xs, uint16_t* 
     plan->lds_bytes = (int32_t)lds;
     return plan->variant < 0 ? hipErrorInvalidValue : hipSuccess;
   }
-#define AQLM_GEMV_KS(MM, C)                                           \
-  return vec ? launch_ks_rb<MM, C, true>(bt, rb_max, nks_min, lds, s) \
-             : launch_ks_rb<MM, C, false>(bt, rb_max, nks_min, lds, s);
-  if (M == 2) {
-    if (copies == 8) AQLM_GEMV_KS(2, 8)
-    return hipErrorInvalidValue;
+#define AQLM_GEMV_KS(MM, C)                                             \
+  {                                                                     \
+    return vec ? launch_ks_rb<MM, C, true>(bt, rb_max, nks_min, lds, s) \
+               : launch_ks_rb<MM, C, false>(bt, rb_max, nks_min, lds, s); \
   }
-  switch (M * 16 + copies) {
-    case 1 * 16 + 16: AQLM_GEMV_KS(1, 16)
-    case 1 * 16 + 8: AQLM_GEMV_KS(1, 8)
-    case 1 * 16 + 4: AQLM_GEMV_KS(1, 4)
-    case 4 * 16 + 16: AQLM_GEMV_KS(4, 16)
-    case 4 * 16 + 8: AQLM_GEMV_KS(4, 8)
-    case 4 * 16 + 4: AQLM_GEMV_KS(4, 4)
-  }
+  if (M == 2 && copies == 8) AQLM_GEMV_KS(2, 8)
+  if (M == 4 && copies == 4) AQLM_GEMV_KS(4, 4)
+  if (M == 1 && copies == 16) AQLM_GEMV_KS(1, 16)
+  if (M == 1 && copies == 8) AQLM_GEMV_KS(1, 8)
+  if (M == 1 && copies == 4) AQLM_GEMV_KS(1, 4)
 #undef AQLM_GEMV_KS
   return hipErrorInvalidValue;
 }
