@@ -26,7 +26,8 @@
 // Row ends.  A row's code bytes need not be a multiple of 16.  The slot that
 // holds the row's last codes loads the row's last 16 bytes and shifts its x
 // slices by as many groups, with zeros for the codes of the slot before; slots
-// wholly past the end load the row's first bytes against x = 0.
+// wholly past the end load the row's first bytes against x = 0.  Both kinds of
+// codes get zero fragments too: an infinite codeword would make NaN of 0.
 //
 // Measured against the general tiled kernel (k_gemm_mfma, four waves per CU, two
 // barriers per 32 codes; chunks of 16 rows) and, for one codebook from 33 rows,
@@ -192,6 +193,13 @@ __global__ __launch_bounds__(KW* kWave) void k_gemm_wide(const GemmWideArgs a) {
       slot_off(j, back);
       const int g0 = wave * kGS + slot * kSlotG - back;
       if constexpr (LDSCB) gather(true, cw[buf], av[buf]);
+      const uint32_t off = (uint32_t)(wave + j * KW) * 64u;
+      if (off + 64u > pitch) {  // the row's last K-slice, partial
+        const int skip = off + (uint32_t)slot * 16u >= pitch ? 8 : back * M;
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+          if (t < skip) av[buf][t] = make_uint4(0, 0, 0, 0);
+      }
 #pragma unroll
       for (int t = 0; t < 8; t += M) {
         const bool valid = t / M >= back;

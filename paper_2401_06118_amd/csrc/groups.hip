@@ -119,7 +119,8 @@ __global__ __launch_bounds__(kGrpThreads) void k_gemv_groups(const GroupLayer L,
 // one wave per row with byte loads of the codes and vector-ALU sums.
 // A row's last, partial slot loads the row's last 16 bytes and skips the codes
 // of the slot before; slots past the end read the row's first bytes against
-// x = 0.
+// x = 0.  In an item with such slots (TAIL) their fragments are zero as well:
+// an infinite codeword would make NaN of 0.
 constexpr int kGmMaxRows = 128;  // rows per workgroup (8 blocks)
 
 template <int M, int G8>
@@ -220,24 +221,33 @@ __global__ __launch_bounds__(kGrpThreads) void k_gemv_groups_mfma(const GroupLay
     slot_off(ks, back);
     // first chunk of the group of this lane's code 0
     const int c0 = ((ks * 4 + slot) * kGroups - back / M) * G8;
+    auto products = [&](auto tail) __attribute__((always_inline)) {
+      constexpr bool TAIL = decltype(tail)::value != 0;
+      const bool past = (uint32_t)ks * 64u + (uint32_t)slot * 16u >= pitch;
 #pragma unroll
-    for (int q = 0; q < kGroups; ++q) {
-      const bool use = r16 == 0 && q * M >= back;
+      for (int q = 0; q < kGroups; ++q) {
+        const bool valid = !TAIL || (!past && q * M >= back);
 #pragma unroll
-      for (int p = 0; p < G8; ++p) {
-        uint4 xb = make_uint4(0, 0, 0, 0);
-        if (use) xb = x_lds[c0 + q * G8 + p];
-        const h8_t xh = __builtin_bit_cast(h8_t, xb);
+        for (int p = 0; p < G8; ++p) {
+          uint4 xb = make_uint4(0, 0, 0, 0);
+          if (r16 == 0 && valid) xb = x_lds[c0 + q * G8 + p];
+          const h8_t xh = __builtin_bit_cast(h8_t, xb);
 #pragma unroll
-        for (int m = 0; m < M; ++m) {
-          const int t = q * M + m;
-          const uint32_t code = (w[t / 4] >> (8 * (t % 4))) & 0xFFu;
-          const uint4 av = my_cb[((p * M + m) * 256 + code) * kCopies];
-          f4_t& a = (m + p) % 2 == 0 ? acc0 : acc1;
-          a = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8_t, av), xh, a, 0, 0, 0);
+          for (int m = 0; m < M; ++m) {
+            const int t = q * M + m;
+            const uint32_t code = (w[t / 4] >> (8 * (t % 4))) & 0xFFu;
+            uint4 av = my_cb[((p * M + m) * 256 + code) * kCopies];
+            if (TAIL && !valid) av = make_uint4(0, 0, 0, 0);
+            f4_t& a = (m + p) % 2 == 0 ? acc0 : acc1;
+            a = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8_t, av), xh, a, 0, 0, 0);
+          }
         }
       }
-    }
+    };
+    if (__builtin_amdgcn_readfirstlane((uint32_t)ks * 64u + 64u) > pitch)
+      products(IntC<1>{});
+    else
+      products(IntC<0>{});
     if (u)
       cw[1] = nw;
     else

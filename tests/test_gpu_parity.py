@@ -877,6 +877,35 @@ def test_gemv_groups_shapes(d_out, d_in, M, g):
     check_products(lay, fp16_to_np(y)[None, :])
 
 
+@pytest.mark.parametrize("d_in,M,B,g,n", [
+    (80, 4, 8, 16, 1),       # larger groups: a last slot with one group, slots past the end
+    (352, 8, 8, 32, 1),
+    (72, 1, 16, 8, 1),       # wide codes, rows that are not whole 16-byte slots
+    (1040, 1, 16, 8, 17),
+    (264, 2, 12, 8, 5),
+    (264, 2, 16, 8, 33),
+])
+def test_infinite_codewords_stay_infinite_at_row_ends(d_in, M, B, g, n):
+    """A row whose first group uses an infinite codeword is infinite with the
+    sign of its x, and no other row is touched, however the row's codes end."""
+    print(f"[inf] d_in={d_in} M={M} B={B} g={g} n={n}", flush=True)
+    lay = synth.layer(33900 + d_in + M + n, 40, d_in, M, B, g=g, n=n)
+    hot = (1 << B) - 1
+    lay.codes[lay.codes == hot] = hot - 1
+    for row, group in ((3, 0), (21, d_in // g - 2), (30, d_in // g - 1)):
+        lay.codes[row, group, 0] = hot
+    lay.codebooks[0, hot, :] = 0
+    lay.codebooks[0, hot, 0] = np.inf
+    lay.scales[:] = np.abs(lay.scales)
+    codes, cb, sc, x = to_device(lay)
+    y = aq().gemv(codes, cb, sc, x[0])[None] if n == 1 else aq().gemm_small_batch(codes, cb, sc, x)
+    y = fp16_to_np(y).astype(np.float64)
+    for row, group in ((3, 0), (21, d_in // g - 2), (30, d_in // g - 1)):
+        sign = np.sign(lay.x[:, group * g].astype(np.float64))
+        assert np.array_equal(y[:, row], sign * np.inf), (row, y[:, row])
+    assert np.isfinite(np.delete(y, [3, 21, 30], axis=1)).all()
+
+
 # ------------------------------------------- small batch over wide codes
 
 @pytest.mark.parametrize("d_out,d_in,M,B,n", [
