@@ -118,7 +118,7 @@ hipError_t launch_gemv_lut(const Layer* Ls, const uint16_t* const* xs, uint16_t*
                            hipStream_t s);
 hipError_t launch_gemm_mfma(const Layer& L, int32_t n, const uint16_t* x, uint16_t* y, hipStream_t s);
 bool mfma_supported(const Layer& L);
-// Wide unpacked codes, 2 to gemm_wide_rows(L) activation rows per launch.
+// Wide unpacked codes, 1 to gemm_wide_rows(L) activation rows per launch.
 int32_t gemm_wide_rows(const Layer& L);
 bool gemm_wide_supported(const Layer& L, int32_t n);
 hipError_t launch_gemm_wide(const Layer& L, int32_t n, const uint16_t* x, uint16_t* y, hipStream_t s);
