@@ -39,7 +39,10 @@
 // the codeword of group slot / 2 and codebook slot % 2 (one 16-byte LDS
 // gather), B the constant that maps (slot, k) to column 8 (slot / 2) + k; so
 // the sum over two codebooks comes out in fp32, exact up to its rounding.
-// Then G * u is added over the tile's columns in registers.
+// Then G * u is added over the tile's columns in registers.  B's zeros meet
+// every codeword of two groups, those past the row (code 0) included, and 0 times
+// an infinity is a NaN: with a codebook that holds an infinity or NaN (found
+// when it is staged) every lane looks its elements up instead.
 //
 // Summation order: the order of a code's pairs and the global atomics vary, so
 // dC and ds agree with the oracle to fp32 accuracy but are not
@@ -110,7 +113,8 @@ template <int M, typename T>
 struct BwLds {  // byte offsets
   static constexpr size_t kCb = 0;                                    // [M][256] codewords
   static constexpr size_t kScales = kCb + (size_t)M * 4096;           // [BM] fp32
-  static constexpr size_t kUnion = kScales + (size_t)T::BM * 4;
+  static constexpr size_t kFlags = kScales + (size_t)T::BM * 4;       // [waves]
+  static constexpr size_t kUnion = kFlags + (size_t)kBwWaves * 4;
   // either the stages ...
   static constexpr size_t kStages = (size_t)kBwStages * T::kStage * 2;
   // ... or a sub-tile's values, codes, counts / offsets and sorted pairs
@@ -195,6 +199,11 @@ __device__ __forceinline__ void bw_interval(const uint16_t* __restrict__ rd, uin
   bw_mfma<T::FM, T::FN>(a0, b0, acc);
 }
 
+// Nonzero if a half of the word is an infinity or NaN.
+__device__ __forceinline__ uint32_t nonfinite_halfs(uint32_t w) {
+  return (uint32_t)((w & 0x7C00u) == 0x7C00u) | (uint32_t)((w & 0x7C000000u) == 0x7C000000u);
+}
+
 template <int M, typename T>
 __global__ __launch_bounds__(kBwThreads) void k_grad_cb(const BwArgs a) {
   using L = BwLds<M, T>;
@@ -219,7 +228,15 @@ __global__ __launch_bounds__(kBwThreads) void k_grad_cb(const BwArgs a) {
   const int wm = wave % T::WM, wn = wave / T::WM;
   const int32_t G = a.d_in / 8;
 
-  for (int e = tid; e < M * 256; e += kBwThreads) reinterpret_cast<uint4*>(lds + L::kCb)[e] = a.cb[e];
+  uint32_t bad = 0;  // halfs with all exponent bits set
+  for (int e = tid; e < M * 256; e += kBwThreads) {
+    const uint4 v = a.cb[e];
+    reinterpret_cast<uint4*>(lds + L::kCb)[e] = v;
+    bad |= nonfinite_halfs(v.x) | nonfinite_halfs(v.y) | nonfinite_halfs(v.z) | nonfinite_halfs(v.w);
+  }
+  // (one word per wave; read in the sub-tiles, barriers later)
+  const uint4* const flags = reinterpret_cast<const uint4*>(lds + L::kFlags);
+  if (const bool any = __any(bad != 0); lane == 0) reinterpret_cast<uint32_t*>(lds + L::kFlags)[wave] = any;
 
   // Fragment read offsets: token 8 slot + r16 / 4 of the half (and 4 more for
   // the second read), column pair p of the tile at position p ^ g.
@@ -386,37 +403,57 @@ __global__ __launch_bounds__(kBwThreads) void k_grad_cb(const BwArgs a) {
           if (e < nv[q]) rank[m][e] = atomicAdd(&count[m * kBwOff + code], 1u);
         }
       // scale gradients of the sub-tile's rows
+      auto scale_grads = [&](auto lookup) __attribute__((always_inline)) {
 #pragma unroll
-      for (int f = 0; f < FMS; ++f) {
-        f4_t dsum = {0.f, 0.f, 0.f, 0.f};
-        const int row16 = wm * 16 * FMS + f * 16;
+        for (int f = 0; f < FMS; ++f) {
+          f4_t dsum = {0.f, 0.f, 0.f, 0.f};
+          const int row16 = wm * 16 * FMS + f * 16;
 #pragma unroll
-        for (int fn = 0; fn < FN; ++fn) {
-          f4_t u = {0.f, 0.f, 0.f, 0.f};
-          const int grp = (wn * FN + fn) * 2 + (slot >> 1);
+          for (int fn = 0; fn < FN; ++fn) {
+            f4_t u = {0.f, 0.f, 0.f, 0.f};
+            if constexpr (decltype(lookup)::value != 0) {
+              int l = lane;  // (opaque, so that nothing of this path is kept in registers outside it)
+              asm volatile("" : "+v"(l));
+              const uint8_t* tc = tcodes + ((row16 + 4 * (l >> 4)) * GT + (wn * FN + fn) * 2 + ((l >> 3) & 1)) * M;
+              const uint16_t* ce = reinterpret_cast<const uint16_t*>(cbl) + (l & 7);
+#pragma unroll 1
+              for (int m = 0; m < M; ++m)
 #pragma unroll
-          for (int m2 = 0; m2 < M; m2 += 2) {
-            const int m = m2 + (slot & 1);
-            uint4 cwd = make_uint4(0, 0, 0, 0);
-            if (M % 2 == 0 || m < M) cwd = cbl[m * 256 + tcodes[((row16 + r16) * GT + grp) * M + m]];
-            u = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8_t, cwd), deal, u, 0, 0, 0);
+                for (int r = 0; r < 4; ++r) u[r] += h2f(ce[(m * 256 + tc[r * GT * M + m]) * 8]);
+            } else {
+              const int grp = (wn * FN + fn) * 2 + (slot >> 1);
+#pragma unroll
+              for (int m2 = 0; m2 < M; m2 += 2) {
+                const int m = m2 + (slot & 1);
+                uint4 cwd = make_uint4(0, 0, 0, 0);
+                if (M % 2 == 0 || m < M) cwd = cbl[m * 256 + tcodes[((row16 + r16) * GT + grp) * M + m]];
+                u = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8_t, cwd), deal, u, 0, 0, 0);
+              }
+            }
+            // (columns past d_in: G there belongs to other columns)
+            if (c0 + (wn * FN + fn) * 16 + r16 < a.d_in) {
+#pragma unroll
+              for (int r = 0; r < 4; ++r) dsum[r] += acc[q * FMS + f][fn][r] * u[r];
+            }
           }
-          // (columns past d_in: G there belongs to other columns)
-          if (c0 + (wn * FN + fn) * 16 + r16 < a.d_in) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) dsum[r] += acc[q * FMS + f][fn][r] * u[r];
+          for (int r = 0; r < 4; ++r) {
+            float v = dsum[r];
+            v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));
+            v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true));
+            v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x141, 0xF, 0xF, true));
+            v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x140, 0xF, 0xF, true));
+            if (r16 == 0) dsl[wn * T::SR + row16 + 4 * slot + r] = v;
           }
         }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          float v = dsum[r];
-          v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));
-          v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true));
-          v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x141, 0xF, 0xF, true));
-          v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x140, 0xF, 0xF, true));
-          if (r16 == 0) dsl[wn * T::SR + row16 + 4 * slot + r] = v;
-        }
-      }
+      };
+      const uint4 fl0 = flags[0], fl1 = flags[1];
+      const int special =
+          __builtin_amdgcn_readfirstlane((int)(fl0.x | fl0.y | fl0.z | fl0.w | fl1.x | fl1.y | fl1.z | fl1.w));
+      if (__builtin_expect(special != 0, 0))
+        scale_grads(IntC<1>{});
+      else
+        scale_grads(IntC<0>{});
       lds_barrier();
 
       // 3. counts to offsets: wave m takes codebook m, four codes per lane

@@ -785,6 +785,43 @@ def test_backward_nonfinite_stays_with_its_codes():
     assert np.isfinite(dcb[:, :200]).all() and np.isfinite(ds[others]).all()
 
 
+@pytest.mark.parametrize("d_out,d_in,M", [
+    (72, 136, 2),       # an odd number of groups: the last 16 columns are half past the row
+    (264, 24, 1),
+    (40, 264, 3),
+    (72, 256, 4),
+])
+def test_backward_infinite_codewords(d_out, d_in, M):
+    """An infinite codeword makes the scale gradient of the rows that use it
+    infinite, with the sign of its product, and touches nothing else; one that
+    no code uses touches nothing at all."""
+    print(f"[backward] infinite codewords d_out={d_out} d_in={d_in} M={M}", flush=True)
+    n, k = 40, 3
+    lay = synth.layer(20500 + d_in + M, d_out, d_in, M, 8, n=n)
+    lay.codes[lay.codes == 0] = 1
+    lay.codes[lay.codes == 255] = 254
+    hot = ((9, 0), (30, d_in // 8 - 1), (33, d_in // 16))
+    for row, group in hot:
+        lay.codes[row, group, M - 1] = 255
+    dy = np.random.default_rng(20501 + d_in).standard_normal((n, d_out)).astype(np.float16)
+    lay.codebooks[:, 0] = 0
+    lay.codebooks[M - 1, 255] = 0
+    ref_cb, ref_ds = oracle.backward(lay.codes, lay.codebooks, lay.scales, lay.x, dy)
+    lay.codebooks[:, 0] = np.inf
+    lay.codebooks[M - 1, 255, k] = -np.inf
+    c, cb, sc, x = to_device(lay)
+    dcb, ds = aq().backward(c, cb, sc, x, torch.from_numpy(dy).cuda())
+    torch.cuda.synchronize()
+    dcb, ds = dcb.double().cpu().numpy(), ds.double().cpu().numpy()
+    assert rel_l2(dcb, ref_cb) <= 1e-4
+    others = np.delete(np.arange(d_out), [row for row, _ in hot])
+    assert np.isfinite(ds[others]).all(), np.flatnonzero(~np.isfinite(ds[others]))
+    assert rel_l2(ds[others], ref_ds[others]) <= 1e-4
+    for row, group in hot:
+        g = dy[:, row].astype(np.float64) @ lay.x[:, group * 8 + k].astype(np.float64)
+        assert ds[row] == -np.sign(g) * np.inf, (row, ds[row], g)
+
+
 def test_backward_accumulates_and_cancelling():
     """Two calls add up (micro-batch accumulation); codebooks that cancel in
     pairs give the same gradients as the oracle."""
