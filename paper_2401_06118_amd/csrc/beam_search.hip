@@ -143,7 +143,8 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// min with a quiet NaN as "no value" (the instruction returns the other one)
+// min with a quiet NaN as "no value" (the instruction returns the other
+// operand; of a signaling NaN it would make a NaN)
 __device__ __forceinline__ double min64(double a, double b) {
   double r;
   asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
@@ -369,7 +370,11 @@ __global__ __launch_bounds__(kBsThreads) void k_beam(const BeamArgs a) {
         for (int u = 0; u < 8; ++u) v = __builtin_fma(hb[t * 8 + u], c[u], v);
         q = __builtin_fma(c[t], v, q);
       }
-      ql[e] = q;
+      // A codeword that is not finite has a quiet NaN for q, so that its scores
+      // are quiet NaNs and absent from every minimum.  An infinite score would
+      // become a signaling NaN with its index in the mantissa, and take the
+      // score it is compared with out of the minimum.
+      ql[e] = __builtin_fabs(q) < __builtin_huge_val() ? q : no_key();
     }
   };
   // element tid of H_jj of group j (tid < 64)

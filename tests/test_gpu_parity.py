@@ -994,9 +994,8 @@ def _beam_inputs(seed, d_out, d_in, M, n_x=64):
 
 @pytest.mark.parametrize("d_out,d_in,M,beam,sweeps", BEAM_CASES)
 def test_beam_search_matches_oracle(d_out, d_in, M, beam, sweeps):
-    """The GPU search scores candidates with fp32 increments, the oracle in
-    fp64, so a near-tie can go either way and the paths may then part: most
-    rows must end on exactly the oracle's codes, every row within 2e-3 of the
+    """The GPU search keeps H r in fp32, the oracle in fp64, so a near-tie can
+    go either way and the paths may then part: most rows must end on exactly the oracle's codes, every row within 2e-3 of the
     oracle's loss, never above its starting loss, and the reported loss must
     be the exact loss of the returned codes."""
     print(f"[beam] d_out={d_out} d_in={d_in} M={M} beam={beam} sweeps={sweeps}", flush=True)
@@ -1053,6 +1052,36 @@ def test_beam_search_shared_workgroups(d_out, d_in, M, beam, sweeps):
     assert np.array_equal(got[zero], ref_codes[zero])
     differ = np.flatnonzero((got != ref_codes).any(axis=(1, 2)))
     assert differ.size <= max(1, d_out // 4), differ
+
+
+@pytest.mark.parametrize("M,beam", [(1, 1), (2, 3), (1, 8)])
+def test_beam_search_passes_over_infinite_codewords(M, beam):
+    """Codewords that score +inf are never taken and hide no other: the search
+    is the one over a codebook that holds far-away codewords in their place."""
+    print(f"[beam] infinite codewords M={M} beam={beam}", flush=True)
+    d_out, d_in = 64, 64
+    rng = np.random.default_rng(31500 + M + beam)
+    lay = synth.layer(31501 + M, d_out, d_in, M, 8)
+    lay.codebooks[:] = -np.abs(lay.codebooks)
+    lay.codebooks[:, 64:128] = 1000     # (a positive codeword against negative weights and a positive H)
+    w = (lay.codebooks[0].astype(np.float32)[rng.integers(0, 64, (d_out, d_in // 8))] * M).reshape(d_out, d_in)
+    w = (w * lay.scales.astype(np.float32)[:, None] * 1.01).astype(np.float32)
+    x = rng.integers(1, 5, size=(d_in, 96)).astype(np.float32)
+    h = (x.astype(np.float64) @ x.T.astype(np.float64)).astype(np.float32)
+    lay.codes[(lay.codes >= 64) & (lay.codes < 128)] -= 64
+    ref_codes, ref_loss = oracle.beam_search(w, h, lay.codes, lay.codebooks, lay.scales, beam=beam, sweeps=1)
+    start = oracle.aq_loss(w, h, lay.codes, lay.codebooks, lay.scales)
+    finite = lay.codebooks.copy()
+    lay.codebooks[:, 64:128] = np.inf
+    codes, cb, sc, _ = to_device(lay)
+    aq().beam_search(torch.from_numpy(w).cuda(), torch.from_numpy(h).cuda(), codes, cb, sc, beam=beam, sweeps=1)
+    torch.cuda.synchronize()
+    got = codes.cpu().numpy()
+    exact = oracle.aq_loss(w, h, got, finite, lay.scales)
+    assert np.all(exact <= start * (1 + 1e-6)), np.flatnonzero(exact > start)
+    differ = np.flatnonzero((got != ref_codes).any(axis=(1, 2)))
+    assert differ.size <= max(1, d_out // 4), differ
+    np.testing.assert_allclose(exact, ref_loss, rtol=2e-3)
 
 
 def test_beam_search_refuses_before_launch():
