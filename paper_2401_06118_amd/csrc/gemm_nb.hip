@@ -310,12 +310,7 @@ hipError_t launch_nb_copies(const GemmNbArgs& a, int nwg, int rb, int rounds, in
   if constexpr (M == 2) {
     if (copies == 8) return launch_nb_rb<M, 8, VEC>(a, nwg, rb, rounds, lds, s);
   }
-  switch (copies) {
-    case 4: return launch_nb_rb<M, 4, VEC>(a, nwg, rb, rounds, lds, s);
-    case 2: return launch_nb_rb<M, 2, VEC>(a, nwg, rb, rounds, lds, s);
-    case 1: return launch_nb_rb<M, 1, VEC>(a, nwg, rb, rounds, lds, s);
-  }
-  return hipErrorInvalidValue;
+  return copies == 4 ? launch_nb_rb<M, 4, VEC>(a, nwg, rb, rounds, lds, s) : hipErrorInvalidValue;
 }
 
 template <int M>
@@ -336,8 +331,8 @@ size_t nb_fixed_lds_m(int M, int n) {
 
 bool gemm_nb_supported(const Layer& L, int32_t n) {
   if (L.B != 8 || !(L.M == 2 || L.M == 4) || n < 2 || n > kMaxTokNB) return false;
-  // at least one codebook copy must fit next to a round of x and the partial tiles
-  return nb_fixed_lds_m(L.M, n) + (size_t)L.M * 256 * 16 <= kLdsLimit;
+  // four codebook copies must fit next to a round of x (or the partial tiles)
+  return nb_fixed_lds_m(L.M, n) + (size_t)L.M * 256 * 16 * 4 <= kLdsLimit;
 }
 
 hipError_t launch_gemm_nb(const Layer& L, int32_t n, const uint16_t* x, uint16_t* y, hipStream_t s) {
@@ -356,12 +351,13 @@ hipError_t launch_gemm_nb(const Layer& L, int32_t n, const uint16_t* x, uint16_t
   const int rounds = (KS + kWavesNB - 1) / kWavesNB;
   const size_t fixed = nb_fixed_lds_m(M, n);
   const size_t per_copy = (size_t)M * 256 * 16;
-  // the conflict-free interleaved layout where it fits, else as many copies as
-  // do (11008 x 4096 4x8 at 16 rows 17.2 -> 14.0 us, at 4
-  // 13.2 -> 11.7; 2x8 at 8 rows 13.7 -> 11.9; 4096 x 11008 4x8 at 16 22.2 -> 18.6)
-  int copies = 16 / M;
-  while (copies > 1 && fixed + per_copy * copies > kLdsLimit) copies /= 2;
+  // The conflict-free interleaved layout where it fits (11008 x 4096 4x8 at 16
+  // rows 17.2 -> 14.0 us, at 4 13.2 -> 11.7; 2x8 at 8 rows 13.7 -> 11.9; 4096 x
+  // 11008 4x8 at 16 22.2 -> 18.6).  Two codebooks beside x of 13 to 16 rows: four
+  // plain copies, with bank conflicts.
+  const int copies = fixed + per_copy * (16 / M) <= kLdsLimit ? 16 / M : 4;
   const size_t lds = fixed + per_copy * copies;
+  if (lds > kLdsLimit) return hipErrorInvalidValue;
   GemmNbArgs a{static_cast<const uint8_t*>(L.codes), reinterpret_cast<const uint4*>(L.codebooks), L.scales,
                reinterpret_cast<const uint4*>(x), y, L.d_out, L.G, n, rows_per_wg, L.tiled ? 1 : 0};
   const bool vec = L.vec_codes;

@@ -326,9 +326,10 @@ __global__ __launch_bounds__(kThreads) void k_gemv_mfma(const GemvBatch bt) {
 // one's x), x is read after it with system-scope loads and y written with
 // system-scope stores (other workgroups of the same grid read it next, from
 // other XCDs); returns false when the wait gave up.
-template <int M, int COPIES, int RB, int D, bool VEC, bool STEP, typename Wait>
+template <int M, int RB, int D, bool VEC, bool STEP, typename Wait>
 __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait&& wait) {
   using C = GCfg<8>;
+  constexpr int COPIES = 16 / M;    // codebook copies
   constexpr int kXS = C::kCPL / M;  // x slices per code slot per K-slice
   // codewords gathered per block before their MFMAs (fewer where the
   // accumulators or, for M = 1, the sixteen x slices take the registers)
@@ -394,7 +395,6 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
   if constexpr (STEP) __syncthreads();
 
   // 1. codebooks, x and scales first (they retire before the code stream).
-  constexpr bool kPairCb = M >= 2 && M * COPIES == 16;
   uint4 cbv = make_uint4(0, 0, 0, 0);
   if (tid < M * 256) cbv = cb[tid];
   // this thread's output row scale, needed only at the end (an unconditional
@@ -464,7 +464,7 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
 #pragma unroll
       for (int k = 0; k < COPIES; ++k) {
         const int c = (k + lane) % COPIES;
-        cb_lds[kPairCb ? (tid & 255) * 16 + (tid >> 8) * COPIES + c : tid * COPIES + c] = cbv;
+        cb_lds[(tid & 255) * 16 + (tid >> 8) * COPIES + c] = cbv;
       }
     }
   };
@@ -474,9 +474,9 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
     load_x();
   }
 
-  // 3. stage codebook copies and x.  With two or four codebooks, 16 / M copies
-  // are interleaved per codeword index: entry e (256 bytes, every 16-byte bank
-  // group once) holds the copies of codebook 0, then those of codebook 1, ...
+  // 3. stage codebook copies and x.  16 / M copies are interleaved per codeword
+  // index: entry e (256 bytes, every 16-byte bank group once) holds the copies
+  // of codebook 0, then those of codebook 1, ...
   // The 16 lanes of a row group gather the M codes of a group (same x, other
   // codebook) in M different orders, so the lanes of one LDS pass read 16
   // different bank groups; each row still gets every codebook over the M
@@ -490,14 +490,10 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
   __syncthreads();  // (no zeroing of the partials: every wave writes all of its slots)
 
   // 4. K-slices of this wave.
-  const uint32_t copy_off = (uint32_t)(lane % COPIES) * 16u;
   const uint32_t cb_base = (uint32_t)(uintptr_t)cb_lds;
-  uint32_t base_m[M];
-#pragma unroll
-  for (int m = 0; m < M; ++m) base_m[m] = cb_base + ((uint32_t)m << 16) + copy_off;
   // interleaved layout: address (code * 16 + m * copies + copy) * 16, with m
   // and the code byte t exchanged by t ^ flip in lane group `flip`
-  const uint32_t flip = kPairCb ? (uint32_t)(r16 / COPIES) : 0u;
+  const uint32_t flip = (uint32_t)(r16 / COPIES);
   uint32_t pbase[M], psel[4];
 #pragma unroll
   for (int tm = 0; tm < M; ++tm)
@@ -505,8 +501,7 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
 #pragma unroll
   for (int k = 0; k < 4; ++k) psel[k] = 0x0C020000u | ((4u + ((uint32_t)k ^ flip)) << 8);
   auto gaddr = [&](uint32_t word, int t) -> uint32_t {
-    if constexpr (kPairCb) return __builtin_amdgcn_perm(word, pbase[t % M], psel[t % 4]);
-    return cw_addr<M, COPIES>(word, t % 4, base_m[t % M], copy_off + cb_base, t % M);
+    return __builtin_amdgcn_perm(word, pbase[t % M], psel[t % 4]);
   };
   {
     f4_t acc[RB];
@@ -625,9 +620,9 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
 }
 
 
-template <int M, int COPIES, int RB, int D, bool VEC>
+template <int M, int RB, int D, bool VEC>
 __global__ __launch_bounds__(kThreads) void k_gemv_ks(const GemvBatch bt) {
-  ks_body<M, COPIES, RB, D, VEC, false>(bt, (int)blockIdx.x, [] { return true; });
+  ks_body<M, RB, D, VEC, false>(bt, (int)blockIdx.x, [] { return true; });
 }
 
 // 1x16 with the codebook in LDS, one 128 KiB chunk (8192 codewords) at a
@@ -909,9 +904,9 @@ hipError_t launch_cb_shape(const GemvBatch& bt, int nks, int rb, hipStream_t s) 
   return hipErrorInvalidValue;
 }
 
-template <int M, int COPIES, int RB, int D, bool VEC>
+template <int M, int RB, int D, bool VEC>
 hipError_t launch_ks(const GemvBatch& bt, size_t lds_bytes, hipStream_t s) {
-  auto kern = k_gemv_ks<M, COPIES, RB, D, VEC>;
+  auto kern = k_gemv_ks<M, RB, D, VEC>;
   {
     const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), 160 * 1024);
     if (e != hipSuccess) return e;
@@ -933,35 +928,35 @@ constexpr int ks_rb_cap(int M) { return M == 1 ? 2 : 7; }
 // Three blocks (three items ahead) fill a one-K-slice ring (q/k/v, two
 // K-slices per wave: 4.824-4.833 -> 4.803-4.814 ms); two blocks keep two
 // K-slices so that both items of the next pair have slots of their own.
-template <int M, int COPIES, int RB, bool VEC>
+template <int M, int RB, bool VEC>
 hipError_t launch_ks_d(const GemvBatch& bt, int nks, size_t lds_bytes, hipStream_t s) {
   constexpr int kDMax = (RB >= 5 || RB == 3) ? 1 : (RB >= 2 ? 2 : 8);
   constexpr int kDMin = RB == 2 ? 2 : 1;
   if constexpr (kDMax >= 8) {
-    if (nks >= 8) return launch_ks<M, COPIES, RB, 8, VEC>(bt, lds_bytes, s);
+    if (nks >= 8) return launch_ks<M, RB, 8, VEC>(bt, lds_bytes, s);
   }
   if constexpr (kDMax >= 4) {
-    if (nks >= 4) return launch_ks<M, COPIES, RB, 4, VEC>(bt, lds_bytes, s);
+    if (nks >= 4) return launch_ks<M, RB, 4, VEC>(bt, lds_bytes, s);
   }
   if constexpr (kDMax >= 2) {
-    if (nks >= 2 || kDMin == 2) return launch_ks<M, COPIES, RB, 2, VEC>(bt, lds_bytes, s);
+    if (nks >= 2 || kDMin == 2) return launch_ks<M, RB, 2, VEC>(bt, lds_bytes, s);
   }
-  return launch_ks<M, COPIES, RB, kDMin, VEC>(bt, lds_bytes, s);
+  return launch_ks<M, RB, kDMin, VEC>(bt, lds_bytes, s);
 }
 
-template <int M, int COPIES, bool VEC>
+template <int M, bool VEC>
 hipError_t launch_ks_rb(const GemvBatch& bt, int rb, int nks, size_t lds_bytes, hipStream_t s) {
   switch (rb) {
-    case 1: return launch_ks_d<M, COPIES, 1, VEC>(bt, nks, lds_bytes, s);
-    case 2: return launch_ks_d<M, COPIES, 2, VEC>(bt, nks, lds_bytes, s);
+    case 1: return launch_ks_d<M, 1, VEC>(bt, nks, lds_bytes, s);
+    case 2: return launch_ks_d<M, 2, VEC>(bt, nks, lds_bytes, s);
   }
   if constexpr (ks_rb_cap(M) >= 7) {
     switch (rb) {
-      case 3: return launch_ks_d<M, COPIES, 3, VEC>(bt, nks, lds_bytes, s);
-      case 4: return launch_ks_d<M, COPIES, 4, VEC>(bt, nks, lds_bytes, s);
-      case 5: return launch_ks_d<M, COPIES, 5, VEC>(bt, nks, lds_bytes, s);
-      case 6: return launch_ks_d<M, COPIES, 6, VEC>(bt, nks, lds_bytes, s);
-      case 7: return launch_ks_d<M, COPIES, 7, VEC>(bt, nks, lds_bytes, s);
+      case 3: return launch_ks_d<M, 3, VEC>(bt, nks, lds_bytes, s);
+      case 4: return launch_ks_d<M, 4, VEC>(bt, nks, lds_bytes, s);
+      case 5: return launch_ks_d<M, 5, VEC>(bt, nks, lds_bytes, s);
+      case 6: return launch_ks_d<M, 6, VEC>(bt, nks, lds_bytes, s);
+      case 7: return launch_ks_d<M, 7, VEC>(bt, nks, lds_bytes, s);
     }
   }
   return hipErrorInvalidValue;
@@ -1003,16 +998,16 @@ hipError_t launch_copies(const GemvBatch& bt, int pf, size_t lds_bytes, hipStrea
 // workgroup stops; a workgroup that sees the flag stops too, so the grid
 // always drains.  The last workgroup to leave resets the counters.
 
-// (M = 2, 8-bit codes, 16-byte code rows) body instantiations: (id, copies,
-// row blocks, ring depth)
+// (M = 2, 8-bit codes, 16-byte code rows) body instantiations: (id, row blocks,
+// ring depth)
 #define AQLM_STEP_VARIANTS(X)                                                                    \
-  X(0, 8, 1, 1) X(1, 8, 1, 2) X(2, 8, 1, 4) X(3, 8, 1, 8) X(4, 8, 2, 2) X(5, 8, 3, 1)             \
-  X(6, 8, 4, 1) X(7, 8, 4, 2) X(8, 8, 5, 1) X(9, 8, 6, 1) X(10, 8, 7, 1)
+  X(0, 1, 1) X(1, 1, 2) X(2, 1, 4) X(3, 1, 8) X(4, 2, 2) X(5, 3, 1) X(6, 4, 1) X(7, 4, 2)         \
+  X(8, 5, 1) X(9, 6, 1) X(10, 7, 1)
 
-int step_variant(int M, int copies, int rb, int d, bool vec) {
+int step_variant(int M, int rb, int d, bool vec) {
   if (M != 2 || !vec) return -1;
-#define AQLM_STEP_FIND(ID, C, R, D) \
-  if (copies == C && rb == R && d == D) return ID;
+#define AQLM_STEP_FIND(ID, R, D) \
+  if (rb == R && d == D) return ID;
   AQLM_STEP_VARIANTS(AQLM_STEP_FIND)
 #undef AQLM_STEP_FIND
   return -1;
@@ -1079,8 +1074,8 @@ __global__ __launch_bounds__(kThreads) void k_gemv_step(const StepLevel* __restr
     const int total = L.bt.total_wgs;
     for (int v = (int)blockIdx.x; ok && v < total; v += nwg) {
       switch (variant) {
-#define AQLM_STEP_CASE(ID, C, R, D) \
-  case ID: ok = ks_body<2, C, R, D, true, true>(L.bt, v, wait); break;
+#define AQLM_STEP_CASE(ID, R, D) \
+  case ID: ok = ks_body<2, R, D, true, true>(L.bt, v, wait); break;
         AQLM_STEP_VARIANTS(AQLM_STEP_CASE)
 #undef AQLM_STEP_CASE
       }
@@ -1290,34 +1285,29 @@ hipError_t gemv_mfma_impl(const Layer* Ls, const uint16_t* const* xs, uint16_t* 
 #undef AQLM_GEMV_L2
     return hipErrorInvalidValue;
   }
-  // One codebook: the most copies that fit next to x and the partials.  Two and
-  // four: 16 / M copies, interleaved, which fit beside every x: two codebooks
-  // against sixteen copies (conflict-free too, twice the staging) Llama-2-7B
-  // decode over tiled codes 211 -> 203 us per 8 blocks, 70B 195 -> 193 per 3
-  // blocks; four against eight plain copies (bank conflicts) 11008 x 4096 at
-  // batch 1 10.7 -> 9.3 us, 4096 x 11008 11.7 -> 10.2 (same box each, the
-  // host side of the call included).
-  const size_t per_copy = (size_t)M * 256 * 16;
-  int copies = 16 / M;
-  while (copies > 1 && base + per_copy * copies > limit) copies /= 2;
-  if (base + per_copy * copies > limit) return hipErrorInvalidValue;
-  const size_t lds = base + per_copy * copies;
+  // 16 / M copies of the codebooks (64 KiB), interleaved: conflict-free gathers,
+  // and they fit beside every x.  Measured for four codebooks against eight
+  // plain copies (bank conflicts): 11008 x 4096 at batch 1 10.7 -> 9.3 us,
+  // 4096 x 11008 11.7 -> 10.2 (same box, the host side of the call included).
+  // For two codebooks, sixteen copies are conflict-free too and the decode steps
+  // of 7B and 70B shapes take the same time within noise; eight are half the
+  // staging.
+  const size_t lds = base + 256 * 16 * 16;
+  if (lds > limit) return hipErrorInvalidValue;
   if (plan) {
     plan->bt = bt;
-    plan->variant = step_variant(M, copies, rb_max, ks_ring_depth(rb_max, nks_min), vec);
+    plan->variant = step_variant(M, rb_max, ks_ring_depth(rb_max, nks_min), vec);
     plan->lds_bytes = (int32_t)lds;
     return plan->variant < 0 ? hipErrorInvalidValue : hipSuccess;
   }
-#define AQLM_GEMV_KS(MM, C)                                             \
-  {                                                                     \
-    return vec ? launch_ks_rb<MM, C, true>(bt, rb_max, nks_min, lds, s) \
-               : launch_ks_rb<MM, C, false>(bt, rb_max, nks_min, lds, s); \
+#define AQLM_GEMV_KS(MM)                                                \
+  return vec ? launch_ks_rb<MM, true>(bt, rb_max, nks_min, lds, s)      \
+             : launch_ks_rb<MM, false>(bt, rb_max, nks_min, lds, s);
+  switch (M) {
+    case 1: AQLM_GEMV_KS(1)
+    case 2: AQLM_GEMV_KS(2)
+    case 4: AQLM_GEMV_KS(4)
   }
-  if (M == 2 && copies == 8) AQLM_GEMV_KS(2, 8)
-  if (M == 4 && copies == 4) AQLM_GEMV_KS(4, 4)
-  if (M == 1 && copies == 16) AQLM_GEMV_KS(1, 16)
-  if (M == 1 && copies == 8) AQLM_GEMV_KS(1, 8)
-  if (M == 1 && copies == 4) AQLM_GEMV_KS(1, 4)
 #undef AQLM_GEMV_KS
   return hipErrorInvalidValue;
 }
