@@ -59,9 +59,10 @@ struct NbCfg {
   static constexpr size_t kPartBytes = (size_t)kWavesNB * 16 * 16 * 4;
 };
 
-template <int M, int COPIES, int RB, int D, bool VEC>
+template <int M, int COPIES, int RB, int D, int ROWS>
 __global__ __launch_bounds__(kThreadsNB) void k_gemm_nb(const GemmNbArgs a) {
   using C = GCfg<8>;
+  constexpr bool VEC = ROWS != kRowBytes;
   using N = NbCfg<M>;
   constexpr int kXS = N::kXS;
   constexpr int kXG = N::kXG;
@@ -179,6 +180,11 @@ __global__ __launch_bounds__(kThreadsNB) void k_gemm_nb(const GemmNbArgs a) {
     if constexpr (kMix) return __builtin_amdgcn_perm(word, base_m[t % M], psel[t % 4]);
     return cw_addr<M, COPIES>(word, t % 4, base_m[t % M], copy_off + cb_base, t % M);
   };
+  auto code_addr = [&](uint32_t word, int t, int left, uint32_t zero_addr) -> uint32_t {
+    const uint32_t at = gaddr(word, t);
+    if constexpr (kMix || ROWS == kRowSlots) return at;
+    return t / M * M < left ? at : zero_addr;
+  };
   f4_t acc[RB];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) acc[rb] = f4_t{0.f, 0.f, 0.f, 0.f};
@@ -202,7 +208,18 @@ __global__ __launch_bounds__(kThreadsNB) void k_gemm_nb(const GemmNbArgs a) {
         lds_barrier();
       }
       const bool live = j < nks;
+      // the K-slice with codes past the row's end, the wave's last (its last
+      // group of x is zero)
+      const bool row_end = wave + j * kWavesNB == KS - 1 && pitch % 64u != 0;
+      const int left = (int)pitch - ((wave + j * kWavesNB) * 64 + (int)slot_off);  // codes of the slot before it
+      const uint32_t zero_addr = (uint32_t)(uintptr_t)(x_lds + (wave + 1) * N::kGS - 1);
       if (live) {
+        if (kMix && row_end) {
+#pragma unroll
+          for (int m = 0; m < M; ++m) base_m[m] = left > 0 ? base_m[m] : zero_addr;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) psel[k] = left > 0 ? psel[k] : kPermBase;
+        }
         const uint4* xs = x_lds + (r16 < n ? r16 : 0) * kXG + wave * N::kGS + slot * kXS;
 #pragma unroll
         for (int s2 = 0; s2 < kXS; ++s2) xr[s2] = r16 < n ? xs[s2] : make_uint4(0, 0, 0, 0);
@@ -210,6 +227,10 @@ __global__ __launch_bounds__(kThreadsNB) void k_gemm_nb(const GemmNbArgs a) {
 #pragma unroll
       for (int rb = 0; rb < RB; rb += 2) {
         const bool pair = rb + 1 < RB;
+        if (ROWS != kRowSlots && kMix && row_end) {
+          repeat_first_group<M>(ring[d][rb], left);
+          if (pair) repeat_first_group<M>(ring[d][pair ? rb + 1 : rb], left);
+        }
         if (live) {
 #pragma unroll
           for (int t0 = 0; t0 < C::kCPL; t0 += kStep) {
@@ -217,8 +238,8 @@ __global__ __launch_bounds__(kThreadsNB) void k_gemm_nb(const GemmNbArgs a) {
 #pragma unroll
             for (int u = 0; u < kStep; ++u) {
               const int t = t0 + u;
-              av[u] = lds_load16(gaddr(ring[d][rb][t / 4], t));
-              if (pair) bv[u] = lds_load16(gaddr(ring[d][pair ? rb + 1 : rb][t / 4], t));
+              av[u] = lds_load16(code_addr(ring[d][rb][t / 4], t, left, zero_addr));
+              if (pair) bv[u] = lds_load16(code_addr(ring[d][pair ? rb + 1 : rb][t / 4], t, left, zero_addr));
             }
 #pragma unroll
             for (int u = 0; u < kStep; ++u) {
@@ -265,9 +286,9 @@ __global__ __launch_bounds__(kThreadsNB) void k_gemm_nb(const GemmNbArgs a) {
   }
 }
 
-template <int M, int COPIES, int RB, int D, bool VEC>
+template <int M, int COPIES, int RB, int D, int ROWS>
 hipError_t launch_nb(const GemmNbArgs& a, int nwg, size_t lds_bytes, hipStream_t s) {
-  auto kern = k_gemm_nb<M, COPIES, RB, D, VEC>;
+  auto kern = k_gemm_nb<M, COPIES, RB, D, ROWS>;
   {
     const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)kLdsLimit);
     if (e != hipSuccess) return e;
@@ -277,40 +298,42 @@ hipError_t launch_nb(const GemmNbArgs& a, int nwg, size_t lds_bytes, hipStream_t
 }
 
 // Code-load ring in rounds (as in the batch-1 kernel): about four items, one
-// round for M = 2 and two row blocks (its x staging registers leave no room).
-template <int M, int COPIES, int RB, bool VEC>
+// round for M = 2 and two row blocks or byte loads (its x staging registers
+// leave no room).
+template <int M, int COPIES, int RB, int ROWS>
 hipError_t launch_nb_d(const GemmNbArgs& a, int nwg, int rounds, size_t lds, hipStream_t s) {
-  constexpr int D4 = RB >= 4 ? 1 : (RB == 1 ? 4 : (M == 2 ? 1 : 2));
-  if (D4 >= 4 && rounds >= 4) return launch_nb<M, COPIES, RB, (D4 >= 4 ? 4 : 1), VEC>(a, nwg, lds, s);
-  if (D4 >= 2 && rounds >= 2) return launch_nb<M, COPIES, RB, (D4 >= 2 ? 2 : 1), VEC>(a, nwg, lds, s);
-  return launch_nb<M, COPIES, RB, 1, VEC>(a, nwg, lds, s);
+  constexpr int D4 = RB >= 4 ? 1 : (M == 2 && (RB == 2 || ROWS == kRowBytes) ? 1 : (RB == 1 ? 4 : 2));
+  if (D4 >= 4 && rounds >= 4) return launch_nb<M, COPIES, RB, (D4 >= 4 ? 4 : 1), ROWS>(a, nwg, lds, s);
+  if (D4 >= 2 && rounds >= 2) return launch_nb<M, COPIES, RB, (D4 >= 2 ? 2 : 1), ROWS>(a, nwg, lds, s);
+  return launch_nb<M, COPIES, RB, 1, ROWS>(a, nwg, lds, s);
 }
 
-// Row blocks per workgroup that fit in registers without spilling.
+// Row blocks per workgroup that fit in registers (M = 2: up to 8 of them go to
+// scratch).
 constexpr int nb_rb_cap(int M) { return M == 2 ? 2 : 4; }
 
-template <int M, int COPIES, bool VEC>
+template <int M, int COPIES, int ROWS>
 hipError_t launch_nb_rb(const GemmNbArgs& a, int nwg, int rb, int rounds, size_t lds, hipStream_t s) {
   switch (rb) {
-    case 1: return launch_nb_d<M, COPIES, 1, VEC>(a, nwg, rounds, lds, s);
-    case 2: return launch_nb_d<M, COPIES, 2, VEC>(a, nwg, rounds, lds, s);
+    case 1: return launch_nb_d<M, COPIES, 1, ROWS>(a, nwg, rounds, lds, s);
+    case 2: return launch_nb_d<M, COPIES, 2, ROWS>(a, nwg, rounds, lds, s);
   }
   if constexpr (nb_rb_cap(M) >= 4) {
     switch (rb) {
-      case 3: return launch_nb_d<M, COPIES, 3, VEC>(a, nwg, rounds, lds, s);
-      case 4: return launch_nb_d<M, COPIES, 4, VEC>(a, nwg, rounds, lds, s);
+      case 3: return launch_nb_d<M, COPIES, 3, ROWS>(a, nwg, rounds, lds, s);
+      case 4: return launch_nb_d<M, COPIES, 4, ROWS>(a, nwg, rounds, lds, s);
     }
   }
   return hipErrorInvalidValue;
 }
 
-template <int M, bool VEC>
+template <int M, int ROWS>
 hipError_t launch_nb_copies(const GemmNbArgs& a, int nwg, int rb, int rounds, int copies, size_t lds,
                             hipStream_t s) {
   if constexpr (M == 2) {
-    if (copies == 8) return launch_nb_rb<M, 8, VEC>(a, nwg, rb, rounds, lds, s);
+    if (copies == 8) return launch_nb_rb<M, 8, ROWS>(a, nwg, rb, rounds, lds, s);
   }
-  return copies == 4 ? launch_nb_rb<M, 4, VEC>(a, nwg, rb, rounds, lds, s) : hipErrorInvalidValue;
+  return copies == 4 ? launch_nb_rb<M, 4, ROWS>(a, nwg, rb, rounds, lds, s) : hipErrorInvalidValue;
 }
 
 template <int M>
@@ -360,13 +383,20 @@ hipError_t launch_gemm_nb(const Layer& L, int32_t n, const uint16_t* x, uint16_t
   if (lds > kLdsLimit) return hipErrorInvalidValue;
   GemmNbArgs a{static_cast<const uint8_t*>(L.codes), reinterpret_cast<const uint4*>(L.codebooks), L.scales,
                reinterpret_cast<const uint4*>(x), y, L.d_out, L.G, n, rows_per_wg, L.tiled ? 1 : 0};
-  const bool vec = L.vec_codes;
-  switch (M) {
-    case 2: return vec ? launch_nb_copies<2, true>(a, nwg, rb, rounds, copies, lds, s)
-                       : launch_nb_copies<2, false>(a, nwg, rb, rounds, copies, lds, s);
-    case 4: return vec ? launch_nb_copies<4, true>(a, nwg, rb, rounds, copies, lds, s)
-                       : launch_nb_copies<4, false>(a, nwg, rb, rounds, copies, lds, s);
+  const int64_t row_bytes = (int64_t)L.G * M;
+  const int ends =
+      !L.vec_codes ? kRowBytes : (row_bytes % (M * copies == 16 ? 16 : 64) == 0 ? kRowSlots : kRowPart);
+#define AQLM_GEMM_NB(MM)                                                                          \
+  switch (ends) {                                                                                 \
+    case kRowSlots: return launch_nb_copies<MM, kRowSlots>(a, nwg, rb, rounds, copies, lds, s);   \
+    case kRowPart: return launch_nb_copies<MM, kRowPart>(a, nwg, rb, rounds, copies, lds, s);     \
+    default: return launch_nb_copies<MM, kRowBytes>(a, nwg, rb, rounds, copies, lds, s);          \
   }
+  switch (M) {
+    case 2: AQLM_GEMM_NB(2)
+    case 4: AQLM_GEMM_NB(4)
+  }
+#undef AQLM_GEMM_NB
   return hipErrorInvalidValue;
 }
 

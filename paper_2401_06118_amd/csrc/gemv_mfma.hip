@@ -326,9 +326,10 @@ __global__ __launch_bounds__(kThreads) void k_gemv_mfma(const GemvBatch bt) {
 // one's x), x is read after it with system-scope loads and y written with
 // system-scope stores (other workgroups of the same grid read it next, from
 // other XCDs); returns false when the wait gave up.
-template <int M, int RB, int D, bool VEC, bool STEP, typename Wait>
+template <int M, int RB, int D, int ROWS, bool STEP, typename Wait>
 __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait&& wait) {
   using C = GCfg<8>;
+  constexpr bool VEC = ROWS != kRowBytes;
   constexpr int COPIES = 16 / M;    // codebook copies
   constexpr int kXS = C::kCPL / M;  // x slices per code slot per K-slice
   // codewords gathered per block before their MFMAs (fewer where the
@@ -524,8 +525,19 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
       for (int d = 0; d < D; ++d) {
         const int j = j0 + d;
         const bool live = j < nks;
+        // the K-slice with codes past the row's end, never in the main loop's
+        // periods (its last group of x is zero)
+        const bool row_end = kIssue != 2 && wave + j * kWaves == KS - 1 && pitch % 64u != 0;
+        const int left = (int)pitch - ((wave + j * kWaves) * 64 + (int)slot_off);  // codes of the slot before it
         if (live) {
           const int ks = wave + j * kWaves;
+          if (row_end) {
+            const uint32_t zero_addr = (uint32_t)(uintptr_t)(x_lds + (xg - 1));
+#pragma unroll
+            for (int tm = 0; tm < M; ++tm) pbase[tm] = left > 0 ? pbase[tm] : zero_addr;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) psel[k] = left > 0 ? psel[k] : kPermBase;
+          }
           if (r16 == 0) {
             const uint4* xs = x_lds + (((uint32_t)ks * C::kKS + (uint32_t)slot * C::kCPL) / M);
 #pragma unroll
@@ -540,6 +552,10 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
 #pragma unroll
         for (int rb = 0; rb < RB; rb += 2) {
           const bool pair = rb + 1 < RB;
+          if (ROWS != kRowSlots && row_end) {
+            repeat_first_group<M>(ring[d][rb], left);
+            if (pair) repeat_first_group<M>(ring[d][pair ? rb + 1 : rb], left);
+          }
           if (live) {
 #pragma unroll
             for (int t0 = 0; t0 < C::kCPL; t0 += kStep) {
@@ -620,9 +636,9 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
 }
 
 
-template <int M, int RB, int D, bool VEC>
+template <int M, int RB, int D, int ROWS>
 __global__ __launch_bounds__(kThreads) void k_gemv_ks(const GemvBatch bt) {
-  ks_body<M, RB, D, VEC, false>(bt, (int)blockIdx.x, [] { return true; });
+  ks_body<M, RB, D, ROWS, false>(bt, (int)blockIdx.x, [] { return true; });
 }
 
 // 1x16 with the codebook in LDS, one 128 KiB chunk (8192 codewords) at a
@@ -904,9 +920,9 @@ hipError_t launch_cb_shape(const GemvBatch& bt, int nks, int rb, hipStream_t s) 
   return hipErrorInvalidValue;
 }
 
-template <int M, int RB, int D, bool VEC>
+template <int M, int RB, int D, int ROWS>
 hipError_t launch_ks(const GemvBatch& bt, size_t lds_bytes, hipStream_t s) {
-  auto kern = k_gemv_ks<M, RB, D, VEC>;
+  auto kern = k_gemv_ks<M, RB, D, ROWS>;
   {
     const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), 160 * 1024);
     if (e != hipSuccess) return e;
@@ -928,35 +944,35 @@ constexpr int ks_rb_cap(int M) { return M == 1 ? 2 : 7; }
 // Three blocks (three items ahead) fill a one-K-slice ring (q/k/v, two
 // K-slices per wave: 4.824-4.833 -> 4.803-4.814 ms); two blocks keep two
 // K-slices so that both items of the next pair have slots of their own.
-template <int M, int RB, bool VEC>
+template <int M, int RB, int ROWS>
 hipError_t launch_ks_d(const GemvBatch& bt, int nks, size_t lds_bytes, hipStream_t s) {
   constexpr int kDMax = (RB >= 5 || RB == 3) ? 1 : (RB >= 2 ? 2 : 8);
   constexpr int kDMin = RB == 2 ? 2 : 1;
   if constexpr (kDMax >= 8) {
-    if (nks >= 8) return launch_ks<M, RB, 8, VEC>(bt, lds_bytes, s);
+    if (nks >= 8) return launch_ks<M, RB, 8, ROWS>(bt, lds_bytes, s);
   }
   if constexpr (kDMax >= 4) {
-    if (nks >= 4) return launch_ks<M, RB, 4, VEC>(bt, lds_bytes, s);
+    if (nks >= 4) return launch_ks<M, RB, 4, ROWS>(bt, lds_bytes, s);
   }
   if constexpr (kDMax >= 2) {
-    if (nks >= 2 || kDMin == 2) return launch_ks<M, RB, 2, VEC>(bt, lds_bytes, s);
+    if (nks >= 2 || kDMin == 2) return launch_ks<M, RB, 2, ROWS>(bt, lds_bytes, s);
   }
-  return launch_ks<M, RB, kDMin, VEC>(bt, lds_bytes, s);
+  return launch_ks<M, RB, kDMin, ROWS>(bt, lds_bytes, s);
 }
 
-template <int M, bool VEC>
+template <int M, int ROWS>
 hipError_t launch_ks_rb(const GemvBatch& bt, int rb, int nks, size_t lds_bytes, hipStream_t s) {
   switch (rb) {
-    case 1: return launch_ks_d<M, 1, VEC>(bt, nks, lds_bytes, s);
-    case 2: return launch_ks_d<M, 2, VEC>(bt, nks, lds_bytes, s);
+    case 1: return launch_ks_d<M, 1, ROWS>(bt, nks, lds_bytes, s);
+    case 2: return launch_ks_d<M, 2, ROWS>(bt, nks, lds_bytes, s);
   }
   if constexpr (ks_rb_cap(M) >= 7) {
     switch (rb) {
-      case 3: return launch_ks_d<M, 3, VEC>(bt, nks, lds_bytes, s);
-      case 4: return launch_ks_d<M, 4, VEC>(bt, nks, lds_bytes, s);
-      case 5: return launch_ks_d<M, 5, VEC>(bt, nks, lds_bytes, s);
-      case 6: return launch_ks_d<M, 6, VEC>(bt, nks, lds_bytes, s);
-      case 7: return launch_ks_d<M, 7, VEC>(bt, nks, lds_bytes, s);
+      case 3: return launch_ks_d<M, 3, ROWS>(bt, nks, lds_bytes, s);
+      case 4: return launch_ks_d<M, 4, ROWS>(bt, nks, lds_bytes, s);
+      case 5: return launch_ks_d<M, 5, ROWS>(bt, nks, lds_bytes, s);
+      case 6: return launch_ks_d<M, 6, ROWS>(bt, nks, lds_bytes, s);
+      case 7: return launch_ks_d<M, 7, ROWS>(bt, nks, lds_bytes, s);
     }
   }
   return hipErrorInvalidValue;
@@ -1004,8 +1020,8 @@ hipError_t launch_copies(const GemvBatch& bt, int pf, size_t lds_bytes, hipStrea
   X(0, 1, 1) X(1, 1, 2) X(2, 1, 4) X(3, 1, 8) X(4, 2, 2) X(5, 3, 1) X(6, 4, 1) X(7, 4, 2)         \
   X(8, 5, 1) X(9, 6, 1) X(10, 7, 1)
 
-int step_variant(int M, int rb, int d, bool vec) {
-  if (M != 2 || !vec) return -1;
+int step_variant(int M, int rb, int d, int rows) {
+  if (M != 2 || rows != kRowSlots) return -1;
 #define AQLM_STEP_FIND(ID, R, D) \
   if (rb == R && d == D) return ID;
   AQLM_STEP_VARIANTS(AQLM_STEP_FIND)
@@ -1075,7 +1091,7 @@ __global__ __launch_bounds__(kThreads) void k_gemv_step(const StepLevel* __restr
     for (int v = (int)blockIdx.x; ok && v < total; v += nwg) {
       switch (variant) {
 #define AQLM_STEP_CASE(ID, R, D) \
-  case ID: ok = ks_body<2, R, D, true, true>(L.bt, v, wait); break;
+  case ID: ok = ks_body<2, R, D, kRowSlots, true>(L.bt, v, wait); break;
         AQLM_STEP_VARIANTS(AQLM_STEP_CASE)
 #undef AQLM_STEP_CASE
       }
@@ -1145,10 +1161,11 @@ hipError_t gemv_mfma_impl(const Layer* Ls, const uint16_t* const* xs, uint16_t* 
   // tiled codes: 8-bit, 16-byte aligned, read by k_gemv_ks alone
   if (Ls[0].tiled && (B != 8 || packed || plan || !Ls[0].vec_codes)) return hipErrorInvalidValue;
   const int kCPL = (B == 8) ? 16 : 8, kKS = 4 * kCPL;
-  bool vec = true;
+  bool vec = true, slots = true;  // slots: every row is whole 16-byte slots
   double total_bytes = 0;
   for (int i = 0; i < count; ++i) {
     vec = vec && Ls[i].vec_codes;
+    slots = slots && (int64_t)Ls[i].G * M % 16 == 0;
     total_bytes += (double)Ls[i].d_out * Ls[i].G * M * code_bytes(B);
   }
   const int cus = num_cus();
@@ -1294,15 +1311,19 @@ hipError_t gemv_mfma_impl(const Layer* Ls, const uint16_t* const* xs, uint16_t* 
   // staging.
   const size_t lds = base + 256 * 16 * 16;
   if (lds > limit) return hipErrorInvalidValue;
+  const int rows = !vec ? kRowBytes : (slots ? kRowSlots : kRowPart);
   if (plan) {
     plan->bt = bt;
-    plan->variant = step_variant(M, rb_max, ks_ring_depth(rb_max, nks_min), vec);
+    plan->variant = step_variant(M, rb_max, ks_ring_depth(rb_max, nks_min), rows);
     plan->lds_bytes = (int32_t)lds;
     return plan->variant < 0 ? hipErrorInvalidValue : hipSuccess;
   }
-#define AQLM_GEMV_KS(MM)                                                \
-  return vec ? launch_ks_rb<MM, true>(bt, rb_max, nks_min, lds, s)      \
-             : launch_ks_rb<MM, false>(bt, rb_max, nks_min, lds, s);
+#define AQLM_GEMV_KS(MM)                                                             \
+  switch (rows) {                                                                    \
+    case kRowSlots: return launch_ks_rb<MM, kRowSlots>(bt, rb_max, nks_min, lds, s); \
+    case kRowPart: return launch_ks_rb<MM, kRowPart>(bt, rb_max, nks_min, lds, s);   \
+    default: return launch_ks_rb<MM, kRowBytes>(bt, rb_max, nks_min, lds, s);        \
+  }
   switch (M) {
     case 1: AQLM_GEMV_KS(1)
     case 2: AQLM_GEMV_KS(2)

@@ -7,6 +7,35 @@
 
 namespace aqlm {
 
+// How the rows of 8-bit codes end, a template parameter (ROWS) of the kernels
+// that run them.  Codes past a row's end meet x = 0, but an infinite codeword
+// would make NaN of that.  So in the wave's last K-slice
+//   - a lane whose slot is past the end reads 16 zero bytes (a group of x past
+//     the end) as every codeword, by the operands of its address permute;
+//   - in a slot that is partly past the end, the codes after the last repeat the
+//     slot's first group, so that they add nothing to a row that is finite (a
+//     row with an infinite codeword right there can become NaN).
+// Without the permute (few codebook copies) every code past the end takes the
+// zero bytes by a select.
+constexpr int kRowBytes = 0;  // any length, loaded byte by byte
+constexpr int kRowSlots = 1;  // whole 16-byte slots (without the permute: whole K-slices)
+constexpr int kRowPart = 2;   // loaded as whole slots (tiled codes of any length)
+
+// The permute's selector in a lane past the row's end: its base as it is.
+constexpr uint32_t kPermBase = 0x03020100u;
+
+// The codes of a slot after its first `left`: its first group again.
+template <int M>
+__device__ __forceinline__ void repeat_first_group(uint32_t (&w)[4], int left) {
+  const uint32_t first = M == 4 ? w[0] : (M == 2 ? (w[0] & 0xFFFFu) * 0x10001u : (w[0] & 0xFFu) * 0x1010101u);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int n = left - 4 * i;
+    const uint32_t keep = n >= 4 ? 0xFFFFFFFFu : (n <= 0 ? 0u : (1u << (8 * n)) - 1u);
+    w[i] = (w[i] & keep) | (first & ~keep);
+  }
+}
+
 template <int B>
 struct GCfg {
   static constexpr int kBpc = code_bytes(B);  // bytes per code

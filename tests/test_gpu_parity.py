@@ -921,26 +921,54 @@ def test_gemv_groups_shapes(d_out, d_in, M, g):
     (1040, 1, 16, 8, 17),
     (264, 2, 12, 8, 5),
     (264, 2, 16, 8, 33),
+    (128, 1, 8, 8, 1),       # 8-bit codes: 16-byte slots, the last K-slice partial
+    (1088, 2, 8, 8, 1),
+    (192, 4, 8, 8, 1),
+    (64, 2, 8, 8, 5),
+    (1088, 4, 8, 8, 16),
+    (72, 1, 8, 8, 1),        # ... rows that are not whole slots
+    (1000, 2, 8, 8, 1),
+    (264, 4, 8, 8, 1),
+    (72, 2, 8, 8, 16),
+    (1000, 4, 8, 8, 5),
+    (8, 2, 8, 8, 17),        # ... one group
 ])
 def test_infinite_codewords_stay_infinite_at_row_ends(d_in, M, B, g, n):
     """A row whose first group uses an infinite codeword is infinite with the
-    sign of its x, and no other row is touched, however the row's codes end."""
+    sign of its x, and no other row is touched, however the row's codes end;
+    an infinite codeword that no code uses touches none (8-bit codes, tiled
+    ones too).  Rows of 8-bit codes that are not whole 16-byte slots need only
+    not be finite: their last slot repeats one of its groups against x = 0."""
     print(f"[inf] d_in={d_in} M={M} B={B} g={g} n={n}", flush=True)
     lay = synth.layer(33900 + d_in + M + n, 40, d_in, M, B, g=g, n=n)
     hot = (1 << B) - 1
     lay.codes[lay.codes == hot] = hot - 1
-    for row, group in ((3, 0), (21, d_in // g - 2), (30, d_in // g - 1)):
+    for row, group in ((3, 0), (21, max(d_in // g - 2, 0)), (30, d_in // g - 1)):
         lay.codes[row, group, 0] = hot
     lay.codebooks[0, hot, :] = 0
     lay.codebooks[0, hot, 0] = np.inf
+    if B == 8 and g == 8:
+        lay.codes[lay.codes == 0] = 1
+        lay.codebooks[:, 0] = np.inf
     lay.scales[:] = np.abs(lay.scales)
     codes, cb, sc, x = to_device(lay)
-    y = aq().gemv(codes, cb, sc, x[0])[None] if n == 1 else aq().gemm_small_batch(codes, cb, sc, x)
-    y = fp16_to_np(y).astype(np.float64)
-    for row, group in ((3, 0), (21, d_in // g - 2), (30, d_in // g - 1)):
-        sign = np.sign(lay.x[:, group * g].astype(np.float64))
-        assert np.array_equal(y[:, row], sign * np.inf), (row, y[:, row])
-    assert np.isfinite(np.delete(y, [3, 21, 30], axis=1)).all()
+    ys = [aq().gemv(codes, cb, sc, x[0])[None] if n == 1 else aq().gemm_small_batch(codes, cb, sc, x)]
+    if B == 8 and g == 8:
+        tiled = aq().TiledCodes(codes, cb, sc)
+        ys.append(torch.empty_like(ys[0]))
+        if n == 1:
+            aq().gemv_tiled_grouped([(tiled, x[0], ys[1][0])])
+        else:
+            ys[1] = tiled.gemm_small_batch(x)
+    for y in ys:
+        y = fp16_to_np(y).astype(np.float64)
+        for row, group in ((3, 0), (21, max(d_in // g - 2, 0)), (30, d_in // g - 1)):
+            sign = np.sign(lay.x[:, group * g].astype(np.float64))
+            if B == 8 and g == 8 and d_in // 8 * M % 16:
+                assert not np.isfinite(y[:, row]).any(), (row, y[:, row])
+            else:
+                assert np.array_equal(y[:, row], sign * np.inf), (row, y[:, row])
+        assert np.isfinite(np.delete(y, [3, 21, 30], axis=1)).all()
 
 
 # ------------------------------------------- small batch over wide codes
