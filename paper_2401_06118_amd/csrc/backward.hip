@@ -41,8 +41,8 @@
 // the sum over two codebooks comes out in fp32, exact up to its rounding.
 // Then G * u is added over the tile's columns in registers.  B's zeros meet
 // every codeword of two groups, those past the row (code 0) included, and 0 times
-// an infinity is a NaN: with a codebook that holds an infinity or NaN (found
-// when it is staged) every lane looks its elements up instead.
+// an infinity is a NaN: infinities and NaNs are staged as zeros, and a workgroup
+// that met any adds their products apart, from the staged s_i * G.
 //
 // Summation order: the order of a code's pairs and the global atomics vary, so
 // dC and ds agree with the oracle to fp32 accuracy but are not
@@ -199,9 +199,31 @@ __device__ __forceinline__ void bw_interval(const uint16_t* __restrict__ rd, uin
   bw_mfma<T::FM, T::FN>(a0, b0, acc);
 }
 
-// Nonzero if a half of the word is an infinity or NaN.
-__device__ __forceinline__ uint32_t nonfinite_halfs(uint32_t w) {
-  return (uint32_t)((w & 0x7C00u) == 0x7C00u) | (uint32_t)((w & 0x7C000000u) == 0x7C000000u);
+// Zeros the halfs of a word that are infinities or NaNs; nonzero if there are any.
+__device__ __forceinline__ uint32_t zero_nonfinite(uint32_t& w) {
+  const uint32_t bad = ((w & 0x7C00u) == 0x7C00u ? 0xFFFFu : 0u) | ((w & 0x7C000000u) == 0x7C000000u ? 0xFFFF0000u : 0u);
+  w &= ~bad;
+  return bad;
+}
+
+// The sum of G * (infinities and NaNs of the codewords) over a thread's `nv`
+// groups of one row: g is s * G of the row's groups (group e at e ^ swz), and the
+// sign of G that of s and s * G (a zero s leaves it in the sign of the zero).
+template <int M>
+__device__ float special_scale_grad(const uint16_t* cb, const uint8_t* codes, const float* g, int first, int swz,
+                                    int nv, float s) {
+  float sum = 0.f;
+#pragma unroll 1
+  for (int b = 0; b < nv * M * 8; ++b) {
+    const int e = b / (8 * M), m = b / 8 % M, k = b % 8;
+    const uint16_t h = cb[(m * 256 + codes[e * M + m]) * 8 + k];
+    if ((h & 0x7C00u) == 0x7C00u) {
+      float v = g[((first + e) ^ swz) * 8 + k];
+      if (s == 0.f) v = __builtin_copysignf(1.f, v);
+      sum += __builtin_copysignf(1.f, s) * v * h2f(h);
+    }
+  }
+  return sum;
 }
 
 template <int M, typename T>
@@ -230,9 +252,9 @@ __global__ __launch_bounds__(kBwThreads) void k_grad_cb(const BwArgs a) {
 
   uint32_t bad = 0;  // halfs with all exponent bits set
   for (int e = tid; e < M * 256; e += kBwThreads) {
-    const uint4 v = a.cb[e];
+    uint4 v = a.cb[e];
+    bad |= zero_nonfinite(v.x) | zero_nonfinite(v.y) | zero_nonfinite(v.z) | zero_nonfinite(v.w);
     reinterpret_cast<uint4*>(lds + L::kCb)[e] = v;
-    bad |= nonfinite_halfs(v.x) | nonfinite_halfs(v.y) | nonfinite_halfs(v.z) | nonfinite_halfs(v.w);
   }
   // (one word per wave; read in the sub-tiles, barriers later)
   const uint4* const flags = reinterpret_cast<const uint4*>(lds + L::kFlags);
@@ -367,6 +389,9 @@ __global__ __launch_bounds__(kBwThreads) void k_grad_cb(const BwArgs a) {
     }
     bw_mfma<FM, FN>(a1, b1, acc);
 
+    const uint4 fl0 = flags[0], fl1 = flags[1];
+    const int special =
+        __builtin_amdgcn_readfirstlane((int)(fl0.x | fl0.y | fl0.z | fl0.w | fl1.x | fl1.y | fl1.z | fl1.w));
     // sub-tiles
 #pragma unroll
     for (int q = 0; q < T::Q; ++q) {
@@ -403,57 +428,44 @@ __global__ __launch_bounds__(kBwThreads) void k_grad_cb(const BwArgs a) {
           if (e < nv[q]) rank[m][e] = atomicAdd(&count[m * kBwOff + code], 1u);
         }
       // scale gradients of the sub-tile's rows
-      auto scale_grads = [&](auto lookup) __attribute__((always_inline)) {
 #pragma unroll
-        for (int f = 0; f < FMS; ++f) {
-          f4_t dsum = {0.f, 0.f, 0.f, 0.f};
-          const int row16 = wm * 16 * FMS + f * 16;
+      for (int f = 0; f < FMS; ++f) {
+        f4_t dsum = {0.f, 0.f, 0.f, 0.f};
+        const int row16 = wm * 16 * FMS + f * 16;
 #pragma unroll
-          for (int fn = 0; fn < FN; ++fn) {
-            f4_t u = {0.f, 0.f, 0.f, 0.f};
-            if constexpr (decltype(lookup)::value != 0) {
-              int l = lane;  // (opaque, so that nothing of this path is kept in registers outside it)
-              asm volatile("" : "+v"(l));
-              const uint8_t* tc = tcodes + ((row16 + 4 * (l >> 4)) * GT + (wn * FN + fn) * 2 + ((l >> 3) & 1)) * M;
-              const uint16_t* ce = reinterpret_cast<const uint16_t*>(cbl) + (l & 7);
-#pragma unroll 1
-              for (int m = 0; m < M; ++m)
+        for (int fn = 0; fn < FN; ++fn) {
+          f4_t u = {0.f, 0.f, 0.f, 0.f};
+          const int grp = (wn * FN + fn) * 2 + (slot >> 1);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) u[r] += h2f(ce[(m * 256 + tc[r * GT * M + m]) * 8]);
-            } else {
-              const int grp = (wn * FN + fn) * 2 + (slot >> 1);
-#pragma unroll
-              for (int m2 = 0; m2 < M; m2 += 2) {
-                const int m = m2 + (slot & 1);
-                uint4 cwd = make_uint4(0, 0, 0, 0);
-                if (M % 2 == 0 || m < M) cwd = cbl[m * 256 + tcodes[((row16 + r16) * GT + grp) * M + m]];
-                u = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8_t, cwd), deal, u, 0, 0, 0);
-              }
-            }
-            // (columns past d_in: G there belongs to other columns)
-            if (c0 + (wn * FN + fn) * 16 + r16 < a.d_in) {
-#pragma unroll
-              for (int r = 0; r < 4; ++r) dsum[r] += acc[q * FMS + f][fn][r] * u[r];
-            }
+          for (int m2 = 0; m2 < M; m2 += 2) {
+            const int m = m2 + (slot & 1);
+            uint4 cwd = make_uint4(0, 0, 0, 0);
+            if (M % 2 == 0 || m < M) cwd = cbl[m * 256 + tcodes[((row16 + r16) * GT + grp) * M + m]];
+            u = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8_t, cwd), deal, u, 0, 0, 0);
           }
+          // (columns past d_in: G there belongs to other columns)
+          if (c0 + (wn * FN + fn) * 16 + r16 < a.d_in) {
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            float v = dsum[r];
-            v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));
-            v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true));
-            v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x141, 0xF, 0xF, true));
-            v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x140, 0xF, 0xF, true));
-            if (r16 == 0) dsl[wn * T::SR + row16 + 4 * slot + r] = v;
+            for (int r = 0; r < 4; ++r) dsum[r] += acc[q * FMS + f][fn][r] * u[r];
           }
         }
-      };
-      const uint4 fl0 = flags[0], fl1 = flags[1];
-      const int special =
-          __builtin_amdgcn_readfirstlane((int)(fl0.x | fl0.y | fl0.z | fl0.w | fl1.x | fl1.y | fl1.z | fl1.w));
-      if (__builtin_expect(special != 0, 0))
-        scale_grads(IntC<1>{});
-      else
-        scale_grads(IntC<0>{});
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          float v = dsum[r];
+          v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));
+          v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true));
+          v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x141, 0xF, 0xF, true));
+          v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x140, 0xF, 0xF, true));
+          if (r16 == 0) dsl[wn * T::SR + row16 + 4 * slot + r] = v;
+        }
+      }
+      // what the codewords' infinities and NaNs add to them
+      if (__builtin_expect(special != 0, 0)) {
+        const int row = (lr / (16 * FMS)) * (16 * FM) + q * 16 * FMS + lr % (16 * FMS);
+        const float v = special_scale_grad<M>(reinterpret_cast<const uint16_t*>(a.cb), tcodes + (lr * GT + gq) * M,
+                                              gl + lr * GT * 8, gq, 2 * ((lr >> 2) & 3), nv[q], tsc[row]);
+        if (v != 0.f) atomicAdd(&a.ds[i0 + row], v);
+      }
       lds_barrier();
 
       // 3. counts to offsets: wave m takes codebook m, four codes per lane
