@@ -74,6 +74,7 @@ constexpr int kBwK = 64;         // tokens per stage
 constexpr int kBwStages = 2;
 constexpr int kBwPairs = 2048;   // (row, group) pairs of a sub-tile
 constexpr int kBwOff = 260;      // offsets kept per codebook (257, padded)
+constexpr int kBwOwn = 32;       // pairs of a class that its thread adds alone
 
 struct BwArgs {
   const uint8_t* codes;  // [d_out][G][M]
@@ -508,20 +509,30 @@ __global__ __launch_bounds__(kBwThreads) void k_grad_cb(const BwArgs a) {
       lds_barrier();
 
       // 5. each class's pairs, two at a time (M = 1: a class's list is shared
-      // by two threads)
+      // by two threads).  A thread adds up to kBwOwn of them (evenly used codes
+      // have 8 on average).
+      auto class_list = [&](int cls, uint32_t& p, uint32_t& end) __attribute__((always_inline)) {
+        const uint32_t* off = count + (cls >> 8) * kBwOff + (cls & 255);
+        p = off[0], end = off[1];
+        if constexpr (M == 1) {
+          const uint32_t mid = (p + end) / 2;
+          if (tid < 256)
+            end = mid;
+          else
+            p = mid;
+        }
+      };
+      uint32_t longs = 0;
 #pragma unroll
       for (int v = 0; v < kClassV; ++v) {
         const int cls = M == 1 ? tid & 255 : tid + v * kBwThreads;
         if (cls < M * 256) {
           const int m = cls >> 8;
-          const uint32_t* off = count + m * kBwOff + (cls & 255);
-          uint32_t p = off[0], end = off[1];
-          if constexpr (M == 1) {
-            const uint32_t mid = (p + end) / 2;
-            if (tid < 256)
-              end = mid;
-            else
-              p = mid;
+          uint32_t p, end;
+          class_list(cls, p, end);
+          if (end - p > (uint32_t)kBwOwn) {
+            longs |= 1u << v;
+            end = p + kBwOwn;
           }
           const uint16_t* lp = list + m * kBwPairs;
           // the sub-tile's sum on its own first (shorter chains of rounding)
@@ -542,6 +553,37 @@ __global__ __launch_bounds__(kBwThreads) void k_grad_cb(const BwArgs a) {
           for (int k = 0; k < 4; ++k) {
             cacc[v][k] += sum0[k];
             cacc[v][4 + k] += sum1[k];
+          }
+        }
+      }
+      // The rest of long lists: the whole wave adds one list after the other
+      // (lane: half of a pair's values).  A thread alone would follow a serial
+      // chain of LDS reads: one code for all pairs, 1024 x 1024 2x8 at 64 tokens,
+      // 431 -> 34 us, a tenth of them one code 57 -> 21.
+      if (__builtin_expect(__ballot(longs != 0) != 0, 0)) {
+#pragma unroll 1
+        for (int v = 0; v < kClassV; ++v) {
+          for (uint64_t rest = __ballot((longs >> v) & 1); rest != 0; rest &= rest - 1) {
+            const int owner = __builtin_ctzll(rest);
+            const int cls = (M == 1 ? (wave * kWave) & 255 : wave * kWave + v * kBwThreads) + owner;
+            uint32_t p, end;
+            class_list(cls, p, end);
+            const uint16_t* lp = list + (cls >> 8) * kBwPairs;
+            f4_t part = {0.f, 0.f, 0.f, 0.f};
+            for (uint32_t i = p + kBwOwn + (lane >> 1); i < end; i += kWave / 2)
+              part += reinterpret_cast<const f4_t*>(gl)[(uint32_t)lp[i] * 2 + (lane & 1)];
+            for (int off = 2; off < kWave; off *= 2)
+#pragma unroll
+              for (int k = 0; k < 4; ++k) part[k] += __shfl_xor(part[k], off);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+              const float pk = part[k % 4];
+              const float w =
+                  __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, pk), k / 4));
+#pragma unroll
+              for (int u = 0; u < kClassV; ++u)
+                if (u == v && lane == owner) cacc[u][k] += w;
+            }
           }
         }
       }

@@ -768,6 +768,24 @@ def test_backward_tiles_splits_and_code_skew(d_out, d_in, M, n, codes):
     assert not dcb.cpu().numpy()[~used].any()  # entries no code uses get nothing
 
 
+@pytest.mark.parametrize("M", [1, 2, 5])
+def test_backward_list_lengths(M):
+    """Codes used by about as many pairs of a sub-tile as a thread adds alone
+    (32; one codebook: two threads per code), and by many more."""
+    print(f"[backward] list lengths M={M}", flush=True)
+    rng = np.random.default_rng(20600 + M)
+    lay = synth.layer(20601 + M, 32, 128, M, 8, n=64)      # one sub-tile of 512 pairs
+    uses = [1, 31, 32, 33, 34, 63, 64, 65, 66, 97]
+    for m in range(M):
+        codes = np.repeat(rng.permutation(256)[:len(uses) + 1], uses + [512 - sum(uses)])
+        lay.codes[:, :, m] = rng.permutation(codes).reshape(32, 16)
+    dy = rng.standard_normal((64, 32)).astype(np.float16)
+    c, cb, sc, x = to_device(lay)
+    dcb, ds = aq().backward(c, cb, sc, x, torch.from_numpy(dy).cuda())
+    torch.cuda.synchronize()
+    _backward_check(lay, dy, dcb, ds)
+
+
 def test_backward_nonfinite_stays_with_its_codes():
     """An infinite upstream gradient reaches the entries its row's codes use
     and no others."""
