@@ -396,7 +396,10 @@ __global__ __launch_bounds__(kBwThreads) void k_grad_cb(const BwArgs a) {
     // sub-tiles
 #pragma unroll
     for (int q = 0; q < T::Q; ++q) {
-      if (q > 0) lds_barrier();  // (the previous sub-tile has been read)
+      if (q > 0) {
+        if (i0 + q * 16 * FMS >= a.d_out) break;  // (no rows in it, nor in the next)
+        lds_barrier();                            // (the previous sub-tile has been read)
+      }
       // 1. s_i * G into LDS: pair (row, group) of the sub-tile at
       // row * GT + (group ^ 2 (row / 4 % 4)), so that the four slots of a
       // store hit different banks; codes; counters to zero.
