@@ -213,7 +213,9 @@ __global__ __launch_bounds__(kThreadsNB) void k_gemm_nb(const GemmNbArgs a) {
       const bool row_end = wave + j * kWavesNB == KS - 1 && pitch % 64u != 0;
       const int left = (int)pitch - ((wave + j * kWavesNB) * 64 + (int)slot_off);  // codes of the slot before it
       const uint32_t zero_addr = (uint32_t)(uintptr_t)(x_lds + (wave + 1) * N::kGS - 1);
+      uint32_t fill = 0;
       if (live) {
+        if (ROWS != kRowSlots && kMix && row_end) fill = finite_codes<M, COPIES>(cb_base, lane);
         if (kMix && row_end) {
 #pragma unroll
           for (int m = 0; m < M; ++m) base_m[m] = left > 0 ? base_m[m] : zero_addr;
@@ -228,8 +230,8 @@ __global__ __launch_bounds__(kThreadsNB) void k_gemm_nb(const GemmNbArgs a) {
       for (int rb = 0; rb < RB; rb += 2) {
         const bool pair = rb + 1 < RB;
         if (ROWS != kRowSlots && kMix && row_end) {
-          repeat_first_group<M>(ring[d][rb], left);
-          if (pair) repeat_first_group<M>(ring[d][pair ? rb + 1 : rb], left);
+          fill_past_end(ring[d][rb], left, fill);
+          if (pair) fill_past_end(ring[d][pair ? rb + 1 : rb], left, fill);
         }
         if (live) {
 #pragma unroll

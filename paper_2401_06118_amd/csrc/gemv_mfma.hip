@@ -504,6 +504,9 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
   auto gaddr = [&](uint32_t word, int t) -> uint32_t {
     return __builtin_amdgcn_perm(word, pbase[t % M], psel[t % 4]);
   };
+  // (by the wave that has the row's last K-slice)
+  uint32_t fill = 0;
+  if (ROWS != kRowSlots && pitch % 16u != 0 && wave == (KS - 1) % kWaves) fill = finite_codes<M, COPIES>(cb_base, lane);
   {
     f4_t acc[RB];
 #pragma unroll
@@ -553,8 +556,8 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
         for (int rb = 0; rb < RB; rb += 2) {
           const bool pair = rb + 1 < RB;
           if (ROWS != kRowSlots && row_end) {
-            repeat_first_group<M>(ring[d][rb], left);
-            if (pair) repeat_first_group<M>(ring[d][pair ? rb + 1 : rb], left);
+            fill_past_end(ring[d][rb], left, fill);
+            if (pair) fill_past_end(ring[d][pair ? rb + 1 : rb], left, fill);
           }
           if (live) {
 #pragma unroll

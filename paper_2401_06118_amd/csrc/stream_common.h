@@ -12,9 +12,8 @@ namespace aqlm {
 // would make NaN of that.  So in the wave's last K-slice
 //   - a lane whose slot is past the end reads 16 zero bytes (a group of x past
 //     the end) as every codeword, by the operands of its address permute;
-//   - in a slot that is partly past the end, the codes after the last repeat the
-//     slot's first group, so that they add nothing to a row that is finite (a
-//     row with an infinite codeword right there can become NaN).
+//   - in a slot that is partly past the end, the codes after the last are set
+//     to codes of finite codewords.
 // Without the permute (few codebook copies) every code past the end takes the
 // zero bytes by a select.
 constexpr int kRowBytes = 0;  // any length, loaded byte by byte
@@ -23,18 +22,6 @@ constexpr int kRowPart = 2;   // loaded as whole slots (tiled codes of any lengt
 
 // The permute's selector in a lane past the row's end: its base as it is.
 constexpr uint32_t kPermBase = 0x03020100u;
-
-// The codes of a slot after its first `left`: its first group again.
-template <int M>
-__device__ __forceinline__ void repeat_first_group(uint32_t (&w)[4], int left) {
-  const uint32_t first = M == 4 ? w[0] : (M == 2 ? (w[0] & 0xFFFFu) * 0x10001u : (w[0] & 0xFFu) * 0x1010101u);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int n = left - 4 * i;
-    const uint32_t keep = n >= 4 ? 0xFFFFFFFFu : (n <= 0 ? 0u : (1u << (8 * n)) - 1u);
-    w[i] = (w[i] & keep) | (first & ~keep);
-  }
-}
 
 template <int B>
 struct GCfg {
@@ -62,6 +49,42 @@ typedef __attribute__((address_space(3))) const u32x4_t lds_v4;
 __device__ __forceinline__ uint4 lds_load16(uint32_t byte_addr) {
   const u32x4_t v = *(lds_v4*)(uintptr_t)byte_addr;
   return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
+// Four code bytes (a whole number of groups) whose codewords are finite, from
+// the interleaved copies at LDS address cb_base; a codebook without a finite
+// codeword gives code 0.  Called by a whole wave.
+template <int M, int COPIES>
+__device__ __forceinline__ uint32_t finite_codes(uint32_t cb_base, int lane) {
+  auto finite = [&](int m, int e) {
+    const uint4 v = lds_load16(cb_base + (uint32_t)(e * 16 + m * COPIES + lane % COPIES) * 16u);
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    uint32_t bad = 0;  // (a half is finite if its exponent bits are not all ones)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bad |= ((w[i] & 0x7C007C00u) + 0x04000400u) & 0x80008000u;
+    return __ballot(bad == 0);
+  };
+  uint64_t any[M];
+#pragma unroll
+  for (int m = 0; m < M; ++m) any[m] = finite(m, lane);
+  uint32_t group = 0;
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    uint32_t first = 0;
+    while (__builtin_expect(any[m] == 0, 0) && first + kWave < 256) any[m] = finite(m, (int)(first += kWave) + lane);
+    if (any[m] != 0) group |= (first + (uint32_t)__builtin_ctzll(any[m])) << (8 * m);
+  }
+  return M == 4 ? group : (M == 2 ? group * 0x10001u : group * 0x1010101u);
+}
+
+// The codes of a slot after its first `left`, replaced by those of `fill`.
+__device__ __forceinline__ void fill_past_end(uint32_t (&w)[4], int left, uint32_t fill) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int n = left - 4 * i;
+    const uint32_t keep = n >= 4 ? 0xFFFFFFFFu : (n <= 0 ? 0u : (1u << (8 * n)) - 1u);
+    w[i] = (w[i] & keep) | (fill & ~keep);
+  }
 }
 
 // LDS byte address of codeword `code` of codebook m for this lane's copy.
