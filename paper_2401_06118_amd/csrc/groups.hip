@@ -14,8 +14,9 @@
 //                     The codebooks sit in LDS (one copy) when they fit
 //                     (up to 128 KiB), else are gathered from L2 (15x8 gs64,
 //                     480 KiB);
-//   k_gemv_groups_mfma  batch 1 where the codebooks fit in LDS, M divides 16
-//                     and x fits beside them (4x8 gs16, 8x8 gs32): matrix cores.
+//   k_gemv_groups_mfma  batch 1 where the codebooks fit in LDS, M divides 16,
+//                     x fits beside them and the layer is large enough
+//                     (4x8 gs16, 8x8 gs32): matrix cores.
 #include "common.h"
 #include "groups.h"
 #include "launch.h"
@@ -269,13 +270,28 @@ size_t gm_lds(const GroupLayer& L, int rows) {
   return GmCfg<M, G8>::kCb + KS * 4 * (16 / M) * G8 * 16 + (size_t)((rows + 15) / 16) * kGrpWaves * 64;
 }
 
+// Whether the matrix-core kernel is the faster one.  It fills 128 KiB of LDS
+// with codebook copies first and an item is a serial chain of 16 G8 gathers;
+// k_gemv_groups copies each codebook once and takes about 0.2 + 0.17 M us per
+// step of a row (64 chunks of 8 inputs) and row of a wave.  At equal rows and
+// inputs, k_gemv_groups -> this kernel in us (4096 rows): one codebook g = 64
+// 1024 inputs 3.8 -> 11.1, 8192 8.8 -> 11.0; 2x8 g = 16 1024 4.0 -> 4.7, 2048
+// 5.0 -> 4.8; 4x8 g = 16 1024 4.8 -> 5.1, 2048 6.7 -> 5.7; 4x8 g = 64 2048 7.1 ->
+// 9.4, 4096 10.5 -> 10.0; 16x8 g = 16 256 6.5 -> 5.4; and at 16384 rows 1x8
+// g = 64 2048 9.4 -> 12.6, 4096 15.2 -> 10.7; 4x8 g = 16 256 7.3 -> 4.8.
+bool groups_mfma_pays(const GroupLayer& L, int G8) {
+  const int64_t cus = num_cus();
+  const int64_t steps = (L.d_out + kGrpWaves * cus - 1) / (kGrpWaves * cus) * ((L.d_in + 511) / 512);
+  return steps * L.M >= 4 * G8 && steps * (L.M + 1) >= 12;
+}
+
 // Launches the matrix-core kernel if it takes the layer.
 template <int M, int G8>
 bool try_groups_mfma(const GroupLayer& L, const uint16_t* x, uint16_t* y, hipStream_t s, hipError_t* e) {
   if constexpr (M * G8 > 32) {
     return false;
   } else {
-    if ((int64_t)(L.d_in / L.g) * M < 16) return false;
+    if ((int64_t)(L.d_in / L.g) * M < 16 || !groups_mfma_pays(L, G8)) return false;
     // rows split evenly over whole rounds of one workgroup per CU
     const int64_t cus = num_cus(), rounds = (L.d_out + kGmMaxRows * cus - 1) / (kGmMaxRows * cus);
     const int rows = (int)((L.d_out + rounds * cus - 1) / (rounds * cus));

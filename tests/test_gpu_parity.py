@@ -919,6 +919,20 @@ def test_calls_follow_the_current_stream():
     (33000, 32, 8, 16),     # two rounds of workgroups
     (40, 96, 3, 32),        # M that does not divide 16 (vector kernel)
     (40, 20480, 8, 32),     # x too large beside the codebooks (vector kernel)
+    # just on the matrix-core side of the size rule, with a last slot of
+    # - one group of four
+    (17, 1040, 4, 16),
+    # - one of eight, fewer items than waves
+    (300, 1552, 2, 16),
+    # - one of two, one row block
+    (7, 528, 8, 16),
+    # - the whole slot
+    (16, 64, 16, 16),
+    # - fifteen of sixteen, more chunks than codes
+    (12300, 4032, 1, 64),
+    # ... and on the other
+    (300, 1536, 2, 16),
+    (40, 512, 8, 16),
 ])
 def test_gemv_groups_shapes(d_out, d_in, M, g):
     print(f"[groups] d_out={d_out} d_in={d_in} M={M} g={g}", flush=True)
@@ -935,6 +949,8 @@ def test_gemv_groups_shapes(d_out, d_in, M, g):
 @pytest.mark.parametrize("d_in,M,B,g,n", [
     (80, 4, 8, 16, 1),       # larger groups: a last slot with one group, slots past the end
     (352, 8, 8, 32, 1),
+    (1040, 4, 8, 16, 1),     # ... on the matrix cores
+    (544, 8, 8, 32, 1),
     (72, 1, 16, 8, 1),       # wide codes, rows that are not whole 16-byte slots
     (1040, 1, 16, 8, 17),
     (264, 2, 12, 8, 5),
