@@ -148,10 +148,22 @@ struct AnyLayer {
 constexpr int64_t kSmallBatchMax = 16;
 constexpr int64_t kChunkedMax = 64;
 // Wide codes run in launches of up to 64 rows (2x12: 32) whose time barely
-// grows with the row count: chunks pay off up to this many rows.
+// grows with the row count: chunks pay off up to this many rows, and above
+// kChunkedMax rows where a row of codes is at least kChunkBytesWide per launch:
+// on shorter ones the launches outweigh the loop over the inputs (1000 rows,
+// one pass of the kernels for more rows -> chunks: 1x16 at 128 rows 256 inputs
+// 9.3 -> 11.3 us, 512 13.3 -> 11.5; 2x16 64 inputs 8.4 -> 9.3, 256 12.1 -> 9.3;
+// 2x12 at 96 rows 256 inputs 13.1 -> 12.3, at 128 256 13.1 -> 16.2, 512 16.6 ->
+// 16.4).
 constexpr int64_t kChunkedMaxWide = 128;
+constexpr int64_t kChunkBytesWide = 64;
 
-// Rows from which two wide codebooks take the prefill kernel.
+// Rows from which two wide codebooks take the prefill kernel rather than the
+// tiled one, which gathers every codeword from LDS or L2 per 16 rows.  Chunks
+// (above) take most of what is below 128 rows: 2x16 from 96 concerns rows of
+// codes shorter than that rule asks for, 2x12 those and 129 to 191 rows (11008 x
+// 4096, tiled kernel / prefill: 128 rows 92 / 134 us, 256 163 / 147, 2048 965 /
+// 551; 2x16 2048 rows 1605 / 623).
 constexpr int64_t kPrefillMin2x12 = 192;
 constexpr int64_t kPrefillMin2xWide = 96;
 
@@ -263,7 +275,11 @@ int gemm_dispatch(const aqlm::Layer& L, int64_t n, const uint16_t* x, uint16_t* 
   // codeword.
   if (aqlm::gemm_wide_supported(L, (int32_t)n)) return status_of(aqlm::launch_gemm_wide(L, (int32_t)n, x, y, s));
   const bool chunk_nb = n <= kChunkedMax && aqlm::gemm_nb_supported(L, (int32_t)kSmallBatchMax);
-  const bool chunk_wide = n <= kChunkedMaxWide && aqlm::gemm_wide_supported(L, 2);
+  bool chunk_wide = n <= kChunkedMaxWide && aqlm::gemm_wide_supported(L, 2);
+  if (chunk_wide && n > kChunkedMax) {
+    const int64_t launches = (n + aqlm::gemm_wide_rows(L) - 1) / aqlm::gemm_wide_rows(L);
+    chunk_wide = (int64_t)L.G * L.M * 2 >= kChunkBytesWide * launches;
+  }
   if (n > kSmallBatchMax && (chunk_nb || chunk_wide)) {
     const int64_t chunk = chunk_nb ? kSmallBatchMax : aqlm::gemm_wide_rows(L);
     for (int64_t t0 = 0; t0 < n; t0 += chunk) {
@@ -275,9 +291,7 @@ int gemm_dispatch(const aqlm::Layer& L, int64_t n, const uint16_t* x, uint16_t* 
   }
   // More tokens: dequantized weight tiles feed a dense MFMA product.  Two
   // wide codebooks gather every codeword from L2 there, which pays off only
-  // from more rows (11008 x 4096, tiled kernel vs prefill: 2x12 92 vs 134 us
-  // at 128 rows, 163 vs 147 at 256, 965 vs 551 at 2048; 2x16 140 vs 153 at
-  // 64, 163 vs 154 at 128, 1605 vs 623 at 2048).
+  // from more rows.
   const int64_t prefill_min = (L.M == 2 && L.B > 8) ? (L.B == 12 ? kPrefillMin2x12 : kPrefillMin2xWide) : 0;
   if (n > kSmallBatchMax && n >= prefill_min && aqlm::prefill_supported(L))
     return status_of(aqlm::launch_prefill(L, (int32_t)n, x, y, s));

@@ -1016,6 +1016,15 @@ def test_infinite_codewords_stay_infinite_at_row_ends(d_in, M, B, g, n):
     (200, 72, 2, 12, 33),       # ... and one row more
     (33, 8, 2, 12, 128),        # rows shorter than a slot (general kernel)
     (64, 520, 2, 16, 128),
+    # more than 64 rows: launches of 64 (2x12: 32) from 64 code bytes a row each,
+    # the general kernels below
+    (1000, 264, 2, 15, 65),
+    (300, 512, 1, 16, 65),
+    (300, 504, 1, 16, 128),
+    (300, 248, 2, 16, 96),
+    (300, 384, 2, 12, 96),
+    (300, 504, 2, 12, 97),
+    (300, 512, 2, 12, 128),
 ])
 def test_gemm_wide_codes_shapes(d_out, d_in, M, B, n):
     print(f"[wide] d_out={d_out} d_in={d_in} M={M} B={B} n={n}", flush=True)
