@@ -489,6 +489,22 @@ def test_gemv_grouped_matches_oracle(shapes, M, B):
     _grouped_case(shapes, M, B, 8000 + M)
 
 
+@pytest.mark.parametrize("d_out,d_in,M,B", [
+    (300, 1032, 1, 16),     # wide codes, rows that are not whole 16-byte slots
+    (300, 1032, 2, 12),
+    (300, 1024, 1, 16),
+    (300, 1032, 2, 8),
+])
+def test_gemv_grouped_single_problem_is_gemv(d_out, d_in, M, B):
+    print(f"[grouped-one] d_out={d_out} d_in={d_in} M={M} B={B}", flush=True)
+    codes, cb, sc, x = to_device(synth.layer(8500 + d_in + B, d_out, d_in, M, B))
+    y = torch.full((d_out,), float("nan"), dtype=torch.float16, device="cuda")
+    aq().gemv_grouped([(codes, cb, sc, x[0], y)])
+    alone = aq().gemv(codes, cb, sc, x[0])
+    torch.cuda.synchronize()
+    assert torch.equal(y.view(torch.int16), alone.view(torch.int16))
+
+
 def test_gemv_grouped_70b_qkv():
     """The Llama-2-70B attention projections as one grouped launch: q
     8192 x 8192, k and v 1024 x 8192 (grouped-query attention), 2x8, checked
