@@ -294,7 +294,8 @@ int aqlm_backward(const void* codes, const uint16_t* codebooks, const uint16_t* 
  * from exact arithmetic).  `loss_out`
  * (fp32 [d_out], may be NULL) receives each row's final loss, recomputed
  * exactly (fp64) from the returned codes.  Rows are searched in parallel (one
- * workgroup per row, the beam state in on-chip memory).
+ * wave per row, up to eight rows per workgroup, the beam state in on-chip
+ * memory).
  * Supported: B = 8, 1 <= M <= 8, g = 8, 1 <= beam <= 8, and
  * 8 * beam * d_in + 2 * beam * d_in / 8 * M + 4096 * M bytes of state within
  * about 158 KiB (d_in up to 2048 with beam 8, 4096 with beam 4); otherwise

@@ -94,11 +94,12 @@ struct BwArgs {
   int32_t split_len;  // tokens per split, a multiple of kBwK
 };
 
-// BM rows x BN inputs per tile, WM x WN waves of FM x FN blocks of 16 x 16; a
-// sub-tile takes FMS of every wave's row blocks.
-template <int BM_, int BN_, int WM_, int WN_, int FMS_>
-struct BwCfg {
-  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, FMS = FMS_;
+// 256 x 128 tiles (rows x inputs), 4 x 2 waves of 64 x 64 in blocks of 16 x 16; a
+// sub-tile takes FMS of every wave's row blocks.  Measured against it (11008 x
+// 4096 2x8, 2048 / 256 tokens, 243 / 99 us): 128 x 128 with waves of 64 x 32 350 /
+// 106 us; 256 x 256 with waves of 128 x 64 520 / 149 us (spills).
+struct BwTile {
+  static constexpr int BM = 256, BN = 128, WM = 4, WN = 2, FMS = 2;
   static constexpr int FM = BM / WM / 16, FN = BN / WN / 16;
   static constexpr int Q = FM / FMS;             // sub-tiles
   static constexpr int SR = WM * 16 * FMS;       // rows of a sub-tile
@@ -110,8 +111,9 @@ struct BwCfg {
   static_assert((BM + BN) / 8 % kBwWaves == 0, "whole load instructions per wave");
 };
 
-template <int M, typename T>
+template <int M>
 struct BwLds {  // byte offsets
+  using T = BwTile;
   static constexpr size_t kCb = 0;                                    // [M][256] codewords
   static constexpr size_t kScales = kCb + (size_t)M * 4096;           // [BM] fp32
   static constexpr size_t kFlags = kScales + (size_t)T::BM * 4;       // [waves]
@@ -227,9 +229,10 @@ __device__ float special_scale_grad(const uint16_t* cb, const uint8_t* codes, co
   return sum;
 }
 
-template <int M, typename T>
+template <int M>
 __global__ __launch_bounds__(kBwThreads) void k_grad_cb(const BwArgs a) {
-  using L = BwLds<M, T>;
+  using T = BwTile;
+  using L = BwLds<M>;
   constexpr int BM = T::BM, BN = T::BN, FM = T::FM, FN = T::FN, FMS = T::FMS, GT = T::GT, PER = T::kPer;
   constexpr int kClassV = (M * 256 + kBwThreads - 1) / kBwThreads;  // (codebook, code) classes per thread
   constexpr int kQuads = GT / 4;                                    // threads per row in the sort
@@ -617,16 +620,11 @@ __global__ __launch_bounds__(kBwThreads) void k_grad_cb(const BwArgs a) {
   }
 }
 
-// 256 x 128 tiles, waves of 64 x 64.  Measured against it (11008 x 4096 2x8,
-// 2048 / 256 tokens, 274 / 99 us): 128 x 128 with waves of 64 x 32 350 / 106
-// us; 256 x 256 with waves of 128 x 64 520 / 149 us (spills).
-typedef BwCfg<256, 128, 4, 2, 2> BwTile;
-
 template <int M>
 hipError_t run_grad(BwArgs a, hipStream_t s) {
   using T = BwTile;
-  auto kern = k_grad_cb<M, T>;
-  constexpr size_t lds = BwLds<M, T>::kTotal;
+  auto kern = k_grad_cb<M>;
+  constexpr size_t lds = BwLds<M>::kTotal;
   const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds);
   if (e != hipSuccess) return e;
   a.tiles_r = (a.d_out + T::BM - 1) / T::BM;

@@ -131,8 +131,8 @@ __device__ __forceinline__ void gf_mfma(const h8_t (&xf)[FM], const h8_t (&wf)[F
 // reads and the LDS sees them spread out (reads and stage writes together take
 // about as many LDS clocks as the MFMAs take).  Same box, against all reads of a
 // phase before its MFMAs: 2048 x 11008 x 4096 178 -> 169 us, 2048 x 8192 x 4096
-// 117 -> 113, 1024 x 11008 x 4096 83 -> 79, 333 x 4096 x 11008 48 -> 45.  With 16
-// waves of 64 x 32 it is slower (512 x 11008 x 4096 53 -> 53, 2048 x 11008 182 ->
+// 117 -> 113, 1024 x 11008 x 4096 83 -> 79; 333 x 4096 x 11008, 192 workgroups of
+// the smaller tiles, stays at 54.  With 16 waves of 64 x 32 it is slower (512 x 11008 x 4096 53 -> 53, 2048 x 11008 182 ->
 // 188): there the other waves fill the gaps.  256 x 256 with 4 waves of 128 x
 // 128 spills (262 us and more).
 template <int FM, int FN, int PER, bool MIX>
