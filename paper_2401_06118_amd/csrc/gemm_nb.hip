@@ -182,7 +182,7 @@ __global__ __launch_bounds__(kThreadsNB) void k_gemm_nb(const GemmNbArgs a) {
   };
   auto code_addr = [&](uint32_t word, int t, int left, uint32_t zero_addr) -> uint32_t {
     const uint32_t at = gaddr(word, t);
-    if constexpr (kMix || ROWS == kRowSlots) return at;
+    if constexpr (kMix || ROWS == kRowWhole) return at;
     return t / M * M < left ? at : zero_addr;
   };
   f4_t acc[RB];
@@ -210,12 +210,12 @@ __global__ __launch_bounds__(kThreadsNB) void k_gemm_nb(const GemmNbArgs a) {
       const bool live = j < nks;
       // the K-slice with codes past the row's end, the wave's last (its last
       // group of x is zero)
-      const bool row_end = wave + j * kWavesNB == KS - 1 && pitch % 64u != 0;
+      const bool row_end = ROWS != kRowWhole && wave + j * kWavesNB == KS - 1 && pitch % 64u != 0;
       const int left = (int)pitch - ((wave + j * kWavesNB) * 64 + (int)slot_off);  // codes of the slot before it
       const uint32_t zero_addr = (uint32_t)(uintptr_t)(x_lds + (wave + 1) * N::kGS - 1);
       uint32_t fill = 0;
       if (live) {
-        if (ROWS != kRowSlots && kMix && row_end) fill = finite_codes<M, COPIES>(cb_base, lane);
+        if ((ROWS == kRowBytes || ROWS == kRowPart) && kMix && row_end) fill = finite_codes<M, COPIES>(cb_base, lane);
         if (kMix && row_end) {
 #pragma unroll
           for (int m = 0; m < M; ++m) base_m[m] = left > 0 ? base_m[m] : zero_addr;
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(kThreadsNB) void k_gemm_nb(const GemmNbArgs a) {
 #pragma unroll
       for (int rb = 0; rb < RB; rb += 2) {
         const bool pair = rb + 1 < RB;
-        if (ROWS != kRowSlots && kMix && row_end) {
+        if ((ROWS == kRowBytes || ROWS == kRowPart) && kMix && row_end) {
           fill_past_end(ring[d][rb], left, fill);
           if (pair) fill_past_end(ring[d][pair ? rb + 1 : rb], left, fill);
         }
@@ -386,10 +386,12 @@ hipError_t launch_gemm_nb(const Layer& L, int32_t n, const uint16_t* x, uint16_t
   GemmNbArgs a{static_cast<const uint8_t*>(L.codes), reinterpret_cast<const uint4*>(L.codebooks), L.scales,
                reinterpret_cast<const uint4*>(x), y, L.d_out, L.G, n, rows_per_wg, L.tiled ? 1 : 0};
   const int64_t row_bytes = (int64_t)L.G * M;
-  const int ends =
-      !L.vec_codes ? kRowBytes : (row_bytes % (M * copies == 16 ? 16 : 64) == 0 ? kRowSlots : kRowPart);
+  const int ends = !L.vec_codes ? kRowBytes
+                   : row_bytes % 64 == 0 ? kRowWhole
+                   : M * copies == 16 && row_bytes % 16 == 0 ? kRowSlots : kRowPart;
 #define AQLM_GEMM_NB(MM)                                                                          \
   switch (ends) {                                                                                 \
+    case kRowWhole: return launch_nb_copies<MM, kRowWhole>(a, nwg, rb, rounds, copies, lds, s);   \
     case kRowSlots: return launch_nb_copies<MM, kRowSlots>(a, nwg, rb, rounds, copies, lds, s);   \
     case kRowPart: return launch_nb_copies<MM, kRowPart>(a, nwg, rb, rounds, copies, lds, s);     \
     default: return launch_nb_copies<MM, kRowBytes>(a, nwg, rb, rounds, copies, lds, s);          \

@@ -506,7 +506,7 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
   };
   // (by the wave that has the row's last K-slice)
   uint32_t fill = 0;
-  if (ROWS != kRowSlots && pitch % 16u != 0 && wave == (KS - 1) % kWaves) fill = finite_codes<M, COPIES>(cb_base, lane);
+  if ((ROWS == kRowBytes || ROWS == kRowPart) && pitch % 16u != 0 && wave == (KS - 1) % kWaves) fill = finite_codes<M, COPIES>(cb_base, lane);
   {
     f4_t acc[RB];
 #pragma unroll
@@ -530,7 +530,8 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
         const bool live = j < nks;
         // the K-slice with codes past the row's end, never in the main loop's
         // periods (its last group of x is zero)
-        const bool row_end = kIssue != 2 && wave + j * kWaves == KS - 1 && pitch % 64u != 0;
+        const bool row_end =
+            ROWS != kRowWhole && kIssue != 2 && wave + j * kWaves == KS - 1 && pitch % 64u != 0;
         const int left = (int)pitch - ((wave + j * kWaves) * 64 + (int)slot_off);  // codes of the slot before it
         if (live) {
           const int ks = wave + j * kWaves;
@@ -555,7 +556,7 @@ __device__ __forceinline__ bool ks_body(const GemvBatch& bt, const int vwg, Wait
 #pragma unroll
         for (int rb = 0; rb < RB; rb += 2) {
           const bool pair = rb + 1 < RB;
-          if (ROWS != kRowSlots && row_end) {
+          if ((ROWS == kRowBytes || ROWS == kRowPart) && row_end) {
             fill_past_end(ring[d][rb], left, fill);
             if (pair) fill_past_end(ring[d][pair ? rb + 1 : rb], left, fill);
           }
@@ -1024,7 +1025,7 @@ hipError_t launch_copies(const GemvBatch& bt, int pf, size_t lds_bytes, hipStrea
   X(8, 5, 1) X(9, 6, 1) X(10, 7, 1)
 
 int step_variant(int M, int rb, int d, int rows) {
-  if (M != 2 || rows != kRowSlots) return -1;
+  if (M != 2 || (rows != kRowSlots && rows != kRowWhole)) return -1;
 #define AQLM_STEP_FIND(ID, R, D) \
   if (rb == R && d == D) return ID;
   AQLM_STEP_VARIANTS(AQLM_STEP_FIND)
@@ -1164,11 +1165,12 @@ hipError_t gemv_mfma_impl(const Layer* Ls, const uint16_t* const* xs, uint16_t* 
   // tiled codes: 8-bit, 16-byte aligned, read by k_gemv_ks alone
   if (Ls[0].tiled && (B != 8 || packed || plan || !Ls[0].vec_codes)) return hipErrorInvalidValue;
   const int kCPL = (B == 8) ? 16 : 8, kKS = 4 * kCPL;
-  bool vec = true, slots = true;  // slots: every row is whole 16-byte slots
+  bool vec = true, slots = true, whole = true;  // every row is whole 16-byte slots, K-slices
   double total_bytes = 0;
   for (int i = 0; i < count; ++i) {
     vec = vec && Ls[i].vec_codes;
     slots = slots && (int64_t)Ls[i].G * M % 16 == 0;
+    whole = whole && (int64_t)Ls[i].G * M % 64 == 0;
     total_bytes += (double)Ls[i].d_out * Ls[i].G * M * code_bytes(B);
   }
   const int cus = num_cus();
@@ -1314,7 +1316,9 @@ hipError_t gemv_mfma_impl(const Layer* Ls, const uint16_t* const* xs, uint16_t* 
   // staging.
   const size_t lds = base + 256 * 16 * 16;
   if (lds > limit) return hipErrorInvalidValue;
-  const int rows = !vec ? kRowBytes : (slots ? kRowSlots : kRowPart);
+  // (whole K-slices apart: with the row-end code in them the 70B decode step of
+  // 12 launches was 0.2 % slower, the 7B one of 32 0.4 %)
+  const int rows = !vec ? kRowBytes : (whole ? kRowWhole : (slots ? kRowSlots : kRowPart));
   if (plan) {
     plan->bt = bt;
     plan->variant = step_variant(M, rb_max, ks_ring_depth(rb_max, nks_min), rows);
@@ -1323,6 +1327,7 @@ hipError_t gemv_mfma_impl(const Layer* Ls, const uint16_t* const* xs, uint16_t* 
   }
 #define AQLM_GEMV_KS(MM)                                                             \
   switch (rows) {                                                                    \
+    case kRowWhole: return launch_ks_rb<MM, kRowWhole>(bt, rb_max, nks_min, lds, s); \
     case kRowSlots: return launch_ks_rb<MM, kRowSlots>(bt, rb_max, nks_min, lds, s); \
     case kRowPart: return launch_ks_rb<MM, kRowPart>(bt, rb_max, nks_min, lds, s);   \
     default: return launch_ks_rb<MM, kRowBytes>(bt, rb_max, nks_min, lds, s);        \

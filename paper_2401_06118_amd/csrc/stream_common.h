@@ -17,8 +17,9 @@ namespace aqlm {
 // Without the permute (few codebook copies) every code past the end takes the
 // zero bytes by a select.
 constexpr int kRowBytes = 0;  // any length, loaded byte by byte
-constexpr int kRowSlots = 1;  // whole 16-byte slots (without the permute: whole K-slices)
+constexpr int kRowSlots = 1;  // whole 16-byte slots (with the permute only)
 constexpr int kRowPart = 2;   // loaded as whole slots (tiled codes of any length)
+constexpr int kRowWhole = 3;  // whole K-slices: nothing is past the end
 
 // The permute's selector in a lane past the row's end: its base as it is.
 constexpr uint32_t kPermBase = 0x03020100u;
