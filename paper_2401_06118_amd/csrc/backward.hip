@@ -49,13 +49,15 @@
 // bit-reproducible from run to run.
 //
 // Measured against the previous kernel (128 x 128 tiles, transposing LDS
-// stores, fp32 LDS atomics): 11008 x 4096 2x8 at 2048 tokens 1095 -> 262 us, at
-// 256 tokens 558 -> 101; 4096 x 11008 4x8 at 2048 1566 -> 300; 4096 x 4096 8x8 at
-// 512 794 -> 125; 2320 x 5112 1x8 at 1515 195 -> 85; 1024 x 1096 2x8 at 4096
-// 160 -> 36.  The contraction runs at about 930 TFLOP/s (matrix cores and LDS
-// reads are of equal length with 64 x 64 waves); the reduction takes about 12
-// us per 256 x 128 tile and CU with two codebooks (sort, gather and stores
-// through LDS, five barriers per sub-tile).
+// stores, fp32 LDS atomics): 11008 x 4096 2x8 at 2048 tokens 1095 -> 245-265 us by
+// box, at 256 tokens 558 -> 93; 4096 x 11008 4x8 at 2048 1566 -> 279; 4096 x 4096 8x8
+// at 512 794 -> 120; 2320 x 5112 1x8 at 1515 195 -> 77; 1024 x 1096 2x8 at 4096
+// 160 -> 30; a layer of one group 8.5 -> 11.4 (outputs cleared in both).  The
+// contraction runs at about 1.0 PFLOP/s (11008 x 4096 2x8 at 2048, 4096 and 8192
+// tokens 266, 428 and 792 us; matrix cores and LDS reads are of equal length with
+// 64 x 64 waves); the rest is about 15 us per 256 x 128 tile and CU with two
+// codebooks (sort, gather and stores through LDS, five barriers per sub-tile).
+// Five to eight codebooks spill 19 to 50 registers.
 #include "common.h"
 #include "launch.h"
 #include "lds_sync.h"
@@ -96,8 +98,9 @@ struct BwArgs {
 
 // 256 x 128 tiles (rows x inputs), 4 x 2 waves of 64 x 64 in blocks of 16 x 16; a
 // sub-tile takes FMS of every wave's row blocks.  Measured against it (11008 x
-// 4096 2x8, 2048 / 256 tokens, 243 / 99 us): 128 x 128 with waves of 64 x 32 350 /
-// 106 us; 256 x 256 with waves of 128 x 64 520 / 149 us (spills).
+// 4096 2x8, 2048 / 256 tokens, when it took 274 / 99 us on the same box): 128 x 128
+// with waves of 64 x 32 350 / 106 us; 256 x 256 with waves of 128 x 64 520 / 149 us
+// (spills).
 struct BwTile {
   static constexpr int BM = 256, BN = 128, WM = 4, WN = 2, FMS = 2;
   static constexpr int FM = BM / WM / 16, FN = BN / WN / 16;

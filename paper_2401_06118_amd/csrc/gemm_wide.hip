@@ -38,6 +38,7 @@
 //   2x12 11008 x 4096   22 / 22 /  50 /  83 /  92 -> 18 / 19 / 23 / 47 / 91
 //   2x12 4096 x 4096    21 / 22 /  43 /  65 /  91 -> 10 / 11 / 13 / 25 / 51
 //   2x12 9000 x 7304    95 / 96 / 186 / 293 / 294 -> 29 / 31 / 38 / 76 / 150
+// (One codebook, 17 to 32 rows and three row blocks: 10 registers spill.)
 #include "common.h"
 #include "launch.h"
 #include "lds_sync.h"
