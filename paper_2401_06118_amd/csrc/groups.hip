@@ -72,6 +72,26 @@ __global__ __launch_bounds__(256) void k_dequant_groups(const GroupLayer L, uint
   }
 }
 
+// One row's product by a whole wave (codebooks `src`, codes `rc`): each lane adds
+// the codeword chunks of its input chunks first, then multiplies them with x.
+__device__ __forceinline__ float group_row_sum(const uint4* src, const uint8_t* __restrict__ rc,
+                                               const uint4* __restrict__ x, uint32_t per_row, uint32_t k, uint32_t M,
+                                               int lane) {
+  float acc = 0.f;
+  for (uint32_t c = (uint32_t)lane; c < per_row; c += kWave) {
+    const uint32_t j = c / k, p = c - j * k;
+    const uint8_t* __restrict__ code = rc + (size_t)j * M;
+    float u[8];
+    set8(src[(uint32_t)code[0] * k + p], u);
+    for (uint32_t m = 1; m < M; ++m) add8(src[((m << 8) + (uint32_t)code[m]) * k + p], u);
+    const uint4 xv = x[c];
+    acc += u[0] * h2f(xv.x & 0xFFFF) + u[1] * h2f(xv.x >> 16) + u[2] * h2f(xv.y & 0xFFFF) +
+           u[3] * h2f(xv.y >> 16) + u[4] * h2f(xv.z & 0xFFFF) + u[5] * h2f(xv.z >> 16) +
+           u[6] * h2f(xv.w & 0xFFFF) + u[7] * h2f(xv.w >> 16);
+  }
+  return wave_sum(acc);
+}
+
 template <bool LDS>
 __global__ __launch_bounds__(kGrpThreads) void k_gemv_groups(const GroupLayer L, const uint4* __restrict__ x,
                                                              uint16_t* __restrict__ y) {
@@ -90,20 +110,7 @@ __global__ __launch_bounds__(kGrpThreads) void k_gemv_groups(const GroupLayer L,
   }
   const uint4* src = LDS ? cb_lds : cb;
   for (int32_t row = blockIdx.x * kGrpWaves + wave; row < L.d_out; row += gridDim.x * kGrpWaves) {
-    const uint8_t* __restrict__ rc = L.codes + (size_t)row * G * M;
-    float acc = 0.f;
-    for (uint32_t c = (uint32_t)lane; c < per_row; c += kWave) {
-      const uint32_t j = c / k, p = c - j * k;
-      const uint8_t* __restrict__ code = rc + (size_t)j * M;
-      float u[8];
-      set8(src[(uint32_t)code[0] * k + p], u);
-      for (uint32_t m = 1; m < M; ++m) add8(src[((m << 8) + (uint32_t)code[m]) * k + p], u);
-      const uint4 xv = x[c];
-      acc += u[0] * h2f(xv.x & 0xFFFF) + u[1] * h2f(xv.x >> 16) + u[2] * h2f(xv.y & 0xFFFF) +
-             u[3] * h2f(xv.y >> 16) + u[4] * h2f(xv.z & 0xFFFF) + u[5] * h2f(xv.z >> 16) +
-             u[6] * h2f(xv.w & 0xFFFF) + u[7] * h2f(xv.w >> 16);
-    }
-    const float sum = wave_sum(acc);
+    const float sum = group_row_sum(src, L.codes + (size_t)row * G * M, x, per_row, k, M, lane);
     if (lane == 0) y[row] = f2h(h2f(L.scales[row]) * sum);
   }
 }
@@ -184,7 +191,9 @@ __global__ __launch_bounds__(kGrpThreads) void k_gemv_groups_mfma(const GroupLay
   u32x4_t cw[2];
   load_codes(wave, cw[0]);
   load_codes(wave + kGrpWaves, cw[1]);
-  const float sc = h2f(L.scales[row0 + (tid < rows ? tid : rows - 1)]);
+  // (the final sums: lane l < 8 of wave w takes row 16 l + w)
+  const int orow = lane * 16 + wave;
+  const float sc = h2f(L.scales[row0 + (orow < rows ? orow : rows - 1)]);
   for (int e = tid; e < xc; e += kGrpThreads) x_lds[e] = e < G * G8 ? x[e] : make_uint4(0, 0, 0, 0);
 #pragma unroll
   for (int i = 0; i < kCbLoads; ++i) {
@@ -256,11 +265,20 @@ __global__ __launch_bounds__(kGrpThreads) void k_gemv_groups_mfma(const GroupLay
   }
   flush();
   __syncthreads();
-  if (tid < rows) {
-    float s = 0.f;
+  float s = 0.f;
+  const bool mine = lane < kGmMaxRows / 16 && orow < rows;
+  if (mine) {
 #pragma unroll
-    for (int v = 0; v < kGrpWaves; ++v) s += part[(tid / 16 * kGrpWaves + v) * 16 + tid % 16];
-    y[row0 + tid] = f2h(sc * s);
+    for (int v = 0; v < kGrpWaves; ++v) s += part[(lane * kGrpWaves + v) * 16 + wave];
+    if (s == s) y[row0 + orow] = f2h(sc * s);
+  }
+  // Rows that came out as NaN again, as k_gemv_groups computes them: x_c infinite
+  // makes infinities of both signs of a group's codewords, their sum only one.
+  for (uint64_t nan = __ballot(mine && s != s); __builtin_expect(nan != 0, 0); nan &= nan - 1) {
+    const int l = __builtin_ctzll(nan);
+    const int32_t row = row0 + l * 16 + wave;
+    const float sum = group_row_sum(cb, L.codes + (size_t)row * pitch, x, (uint32_t)(G * G8), G8, M, lane);
+    if (lane == l) y[row] = f2h(sc * sum);
   }
 }
 

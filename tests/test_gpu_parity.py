@@ -962,6 +962,29 @@ def test_gemv_groups_shapes(d_out, d_in, M, g):
     check_products(lay, fp16_to_np(y)[None, :])
 
 
+@pytest.mark.parametrize("d_out,d_in,M,g", [
+    (72, 64, 4, 16),        # one wave per row
+    (72, 1088, 2, 16),
+    (72, 1088, 4, 16),      # on the matrix cores
+    (300, 2064, 4, 16),
+    (300, 2048, 8, 32),
+    (300, 128, 16, 16),
+])
+def test_gemv_groups_infinite_x(d_out, d_in, M, g):
+    """An infinite input makes every row infinite, with the sign of its weight:
+    a group's codewords are added before they meet x."""
+    print(f"[groups-inf] d_out={d_out} d_in={d_in} M={M} g={g}", flush=True)
+    lay = synth.layer(34100 + d_out + d_in + M, d_out, d_in, M, 8, g=g)
+    at = 5 * g + 3 if d_in > 5 * g + 3 else 3
+    lay.x[0, at] = -np.inf
+    codes, cb, sc, x = to_device(lay)
+    y = fp16_to_np(aq().gemv(codes, cb, sc, x[0])).astype(np.float64)
+    w = sum(lay.codebooks[m].astype(np.float64)[lay.codes[:, at // g, m].astype(np.int64), at % g] for m in range(M))
+    w = w * lay.scales.astype(np.float64)
+    assert (w != 0).all()
+    assert np.array_equal(y, -np.sign(w) * np.inf), np.flatnonzero(y != -np.sign(w) * np.inf)
+
+
 @pytest.mark.parametrize("d_in,M,B,g,n", [
     (80, 4, 8, 16, 1),       # larger groups: a last slot with one group, slots past the end
     (352, 8, 8, 32, 1),
