@@ -20,6 +20,7 @@
 #include "common.h"
 #include "groups.h"
 #include "launch.h"
+#include "lds_sync.h"
 
 namespace aqlm {
 
@@ -129,7 +130,7 @@ __global__ __launch_bounds__(kGrpThreads) void k_gemv_groups(const GroupLayer L,
 // of the slot before; slots past the end read the row's first bytes against
 // x = 0.  In an item with such slots (TAIL) their fragments are zero as well:
 // an infinite codeword would make NaN of 0.
-constexpr int kGmMaxRows = 128;  // rows per workgroup (8 blocks)
+constexpr int kGmMaxRows = 2 * kWave;  // rows per workgroup (8 blocks; two waves store them)
 
 template <int M, int G8>
 struct GmCfg {
@@ -191,9 +192,7 @@ __global__ __launch_bounds__(kGrpThreads) void k_gemv_groups_mfma(const GroupLay
   u32x4_t cw[2];
   load_codes(wave, cw[0]);
   load_codes(wave + kGrpWaves, cw[1]);
-  // (the final sums: lane l < 8 of wave w takes row 16 l + w)
-  const int orow = lane * 16 + wave;
-  const float sc = h2f(L.scales[row0 + (orow < rows ? orow : rows - 1)]);
+  const float sc = h2f(L.scales[row0 + (tid < rows ? tid : rows - 1)]);
   for (int e = tid; e < xc; e += kGrpThreads) x_lds[e] = e < G * G8 ? x[e] : make_uint4(0, 0, 0, 0);
 #pragma unroll
   for (int i = 0; i < kCbLoads; ++i) {
@@ -265,20 +264,28 @@ __global__ __launch_bounds__(kGrpThreads) void k_gemv_groups_mfma(const GroupLay
   }
   flush();
   __syncthreads();
-  float s = 0.f;
-  const bool mine = lane < kGmMaxRows / 16 && orow < rows;
-  if (mine) {
+  // Rows that come out as NaN are computed again as k_gemv_groups does: x_c
+  // infinite makes infinities of both signs of a group's codewords, their sum only
+  // one.  Their mask goes through the space of x, so that all waves share them.
+  uint64_t* const nan = reinterpret_cast<uint64_t*>(x_lds);
+  if (wave < kGmMaxRows / kWave) {
+    float s = 0.f;
+    if (tid < rows) {
 #pragma unroll
-    for (int v = 0; v < kGrpWaves; ++v) s += part[(lane * kGrpWaves + v) * 16 + wave];
-    if (s == s) y[row0 + orow] = f2h(sc * s);
+      for (int v = 0; v < kGrpWaves; ++v) s += part[(tid / 16 * kGrpWaves + v) * 16 + tid % 16];
+      if (s == s) y[row0 + tid] = f2h(sc * s);
+    }
+    const uint64_t bad = __ballot(s != s);
+    if (lane == 0) nan[wave] = bad;
   }
-  // Rows that came out as NaN again, as k_gemv_groups computes them: x_c infinite
-  // makes infinities of both signs of a group's codewords, their sum only one.
-  for (uint64_t nan = __ballot(mine && s != s); __builtin_expect(nan != 0, 0); nan &= nan - 1) {
-    const int l = __builtin_ctzll(nan);
-    const int32_t row = row0 + l * 16 + wave;
+  lds_barrier();
+  const uint64_t bad0 = nan[0], bad1 = nan[1];
+  if (__builtin_expect((bad0 | bad1) == 0, 1)) return;
+  for (int r = wave; r < rows; r += kGrpWaves) {
+    if ((((r < kWave ? bad0 : bad1) >> (r % kWave)) & 1) == 0) continue;
+    const int32_t row = row0 + r;
     const float sum = group_row_sum(cb, L.codes + (size_t)row * pitch, x, (uint32_t)(G * G8), G8, M, lane);
-    if (lane == l) y[row] = f2h(sc * sum);
+    if (lane == 0) y[row] = f2h(h2f(L.scales[row]) * sum);
   }
 }
 
