@@ -215,9 +215,10 @@ int aqlm_gemm_small_batch_tiled(const void* codes, const uint16_t* codebooks, co
 /* Product with n activation rows: y[t][i] = fp16(s_i * sum_c W[i][c] x[t][c])
  * with W reconstructed as above, fp32 accumulation, any n >= 1 (the batched
  * and prefill products of a layer; the paper times the single-row case,
- * Sec. 4.3).  n = 1 runs the matrix-vector kernel; 2..16 rows put the rows in
- * the matrix-core (MFMA) columns of the same scheme, and up to 64 rows (32
- * for 1x16) run as chunks of 16; more rows dequantize weight tiles into
+ * Sec. 4.3).  n = 1 runs the matrix-vector kernel; two or four codebooks of 8-bit
+ * codes put 2..16 rows in the matrix-core (MFMA) columns of the same scheme, up
+ * to 64 rows as chunks of 16; codes wider than 8 bits run up to 128 rows in
+ * launches of 64 (2x12: 32); more rows dequantize weight tiles into
  * on-chip memory once per tile of 128 or 256 rows of x and feed them to dense
  * fp16 MFMA products.  Needs no workspace.  Results are
  * within fp32-accumulation accuracy of fp16(W) x, not bit-exact with it.

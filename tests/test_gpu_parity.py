@@ -286,6 +286,10 @@ def test_gemm_small_batch_shapes(d_out, d_in, M, n):
     (300, 1040, 2, 8, 17), (300, 1040, 4, 8, 300), (129, 520, 1, 8, 40), (1000, 4096, 2, 8, 256),
     (1000, 4096, 4, 8, 513), (260, 4104, 1, 16, 100), (128, 64, 4, 8, 257), (4096, 512, 2, 8, 1024),
     (7, 2056, 1, 16, 33),
+    # wide codes past the wide small-batch kernel's 128 rows, rows that are and are
+    # not whole 16-byte slots (2x12 up to 191: the general tiled kernel)
+    (260, 4104, 1, 16, 130), (140, 2048, 2, 15, 129), (300, 2056, 2, 16, 140), (300, 2056, 2, 12, 150),
+    (140, 2048, 2, 12, 129), (300, 2056, 2, 12, 192),
 ])
 def test_prefill_shapes(d_out, d_in, M, B, n):
     """Many tokens: ragged row and token tiles, K not a multiple of the
@@ -1298,9 +1302,9 @@ def test_2x12_dequantize_special_values_bit_exact():
 @pytest.mark.parametrize("B", [12, 15, 16])
 @pytest.mark.parametrize("n", [4, 16, 32, 100, 200, 300])
 def test_2xwide_gemm_matches_oracle(B, n):
-    """Small batch (chunks of 16), the tiled kernel, the prefill kernel with
-    two codebooks gathered from L2 (from 96 rows, 192 for 2x12; ragged row
-    and token tiles) and the workspace path."""
+    """Small batch (the wide-code kernel up to 128 rows, in launches of 64 or
+    32), the prefill kernel with two codebooks gathered from L2 (above; ragged
+    row and token tiles) and the workspace path."""
     print(f"[2x{B} gemm] n={n}", flush=True)
     lay = synth.layer(17_900 + B + n, 1100, 2048, 2, B, n=n)
     codes, cb, sc, x = to_device(lay)
